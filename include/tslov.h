@@ -83,7 +83,8 @@ typedef enum tslov_flag {
 typedef struct tslov_info {
     int k_used;          /* Krylov size reached (< k after a lucky breakdown)           */
     int breakdown;       /* 0 none, 1 lucky (invariant Krylov space), 2 serious           */
-    int newton_iters;    /* iterations of the projected-matrix sign step                 */
+    int newton_iters;    /* iterations of the projected-matrix sign step (Newton iterations, or
+                            the pole sets, 1 or 2, that the rational step of a sign call took) */
     int cg_iters;        /* iterations of the shifted solves of a deflated derivative (else 0) */
     int flags;           /* tslov_flag bits                                              */
     int reserved;
@@ -320,7 +321,7 @@ tslov_status tslov_lanczos_matrix(tslov_ctx* ctx, const void* psi, int k, void* 
  * the projected matrix): c_out = sgn(T) e_1 for the k x k complex tridiagonal T with
  *   T_jj = diag[j] (k complex), T_{j+1,j} = sub[j] (k-1 real), T_{j,j+1} = sup[j] (k-1 complex),
  * host arrays of interleaved (re, im) doubles; c_out: device, k complex128.  Runs the
- * same scaled Newton iteration as tslov_sign.  ERR_SIGN_UNDEFINED when an eigenvalue
+ * same projected-matrix step as tslov_sign.  ERR_SIGN_UNDEFINED when an eigenvalue
  * of T has |Re| <= 1e-12 times the infinity norm of T (info->min_abs_re_ritz). */
 tslov_status tslov_tridiag_sign(tslov_ctx* ctx, int k, const double* diag, const double* sub, const double* sup,
                                 void* c_out, tslov_info* info);

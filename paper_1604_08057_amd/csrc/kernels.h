@@ -324,6 +324,23 @@ void nest_block(const NestWork& nw, const DenseWork& w2, int m, hipStream_t st);
 // coef.c[1..k] = T V' (T')^{1/2} e_1 from X = sgn([[0, T'], [I, 0]]).
 void nest_finish(const NestWork& nw, const DenseWork& w2, Coef coef, int k, int m, hipStream_t st);
 
+// ---------------------------------------------------------------- rational step
+// Workspace of the partial-fraction sign step (ratsign.hip): per entry of the list a
+// plane of kcap rows of ld poles, two partials per row, and acc: |dc|^2 and |c|^2, dc the
+// difference of the two members whose mean is c.
+struct RatWork {
+    ZD* mem;
+    double* rows;
+    double* acc;
+    size_t ld;
+    int kcap;
+    __host__ __device__ ZD* buf(int e) const { return mem + (size_t)e * kcap * ld; }
+    __host__ __device__ double* part(int e) const { return rows + (size_t)e * 2 * kcap; }
+};
+// coef.c = sgn(T) e_1 of every entry (k[e] = k_used, decreasing) by the N-point rational
+// sign (N a multiple of 4), the accuracy estimates into w.acc.
+void launch_ratsign(Coef coef, const SrcList& L, const RatWork& w, int N, hipStream_t st);
+
 // c = X e_1, adjoint seeds from Y, S = |x| Re sum_j c_j h_j.
 void launch_dense_extract(Coef coef, const SrcList& L, int grad, const DenseWork& w, hipStream_t st);
 
