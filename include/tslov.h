@@ -133,15 +133,12 @@ tslov_status tslov_apply_h(tslov_ctx* ctx, const void* in, void* out, int dagger
 /* tslov_apply_h without any device allocation, for callers that cannot allocate
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): the same operator, same arguments and same result bits as
- * tslov_apply_h, with its two staging fields in a static device array of 32 MiB
- * that each device holds for the life of the process, instead of the context's
- * workspace.  The lattice must fit it: 2 * 12 * V complex values of the context
- * precision (float64 / float32-link contexts: V <= 87381, e.g. up to 16^4; float32:
- * twice that), else ERR_ARG.  It never times launches and never picks the
- * marching chunk length by timing (it uses the context's pick if one was made,
- * else the built-in choice).  Every call on a device shares that device's array:
- * calls that overlap on one device (other streams, other contexts, other threads)
- * race on it and must be serialised by the caller. */
+ * tslov_apply_h, for lattices of at most 32 MiB of fields: 2 * 12 * V complex values
+ * of the context precision (float64 / float32-link contexts: V <= 87381, e.g. up to
+ * 16^4; float32: twice that), else ERR_ARG.  It never times launches and never picks
+ * the marching chunk length by timing (it uses the context's pick if one was made,
+ * else the built-in choice).  It uses no workspace: calls of different contexts,
+ * streams or threads do not disturb each other. */
 tslov_status tslov_apply_h_noalloc(tslov_ctx* ctx, const void* in, void* out, int dagger);
 
 /* Optional deflation by known eigenpairs of H (Sec. 3: the standard projection
@@ -469,8 +466,8 @@ tslov_status tslov_timing_read(tslov_ctx* ctx, int which, int* count, double* to
 tslov_status tslov_set_graphs(tslov_ctx* ctx, int on);
 
 /* Launch shape of the operator (tslov_apply_dw / tslov_apply_h) on lattices whose
- * t-slices split into whole tiles of 128 sites over the 8 XCDs (e.g. 32^4): each
- * thread marches through T consecutive t-slices.  T = 0 (the default) lets the
+ * t-slices split evenly over the 8 XCDs in multiples of 128 sites (e.g. 32^4): each
+ * workgroup marches through T consecutive t-slices.  T = 0 (the default) lets the
  * first call time the candidates (divisors of N_t giving 128 to 4096 workgroups,
  * best of three launches each) and keep the fastest for the context; T > 0
  * forces that chunk length.  Results do not depend on T.  ERR_ARG unless T = 0

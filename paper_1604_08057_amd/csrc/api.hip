@@ -115,37 +115,9 @@ std::vector<int> site_block_order(const Geom& g, int& nwg) {
 
 }  // namespace
 
-// Device memory of the allocation-free operator entry point: the two structure-
-// of-arrays staging fields (input and output of the stencil) for lattices of up
-// to kScratchBytes / (2 * 12 * sizeof(complex)) sites.  Each device holds its own
-// copy while the process lives; host code reaches it only through the address
-// hipGetSymbolAddress returns for that device (the array's name is a host-side
-// stand-in, not a device address).
-constexpr size_t kScratchBytes = (size_t)32 << 20;
-static __device__ __align__(256) char scratch[kScratchBytes];
-
-namespace {
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mu;
-char* g_scratch_ptr[kMaxDevices] = {};
-
-// The scratch address on the current device `dev`, looked up once per device.
-tslov_status scratch_address(int dev, char** out) {
-    if (dev < 0 || dev >= kMaxDevices) return fail(TSLOV_ERR_ARG, "device index out of range");
-    std::lock_guard<std::mutex> lk(g_scratch_mu);
-    if (!g_scratch_ptr[dev]) {
-        void* p = nullptr;
-        const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-        if (e != hipSuccess || !p) {
-            (void)hipGetLastError();
-            return fail(TSLOV_ERR_HIP, std::string("hipGetSymbolAddress(scratch): ") + hipGetErrorString(e));
-        }
-        g_scratch_ptr[dev] = static_cast<char*>(p);
-    }
-    *out = g_scratch_ptr[dev];
-    return TSLOV_OK;
-}
-}  // namespace
+// Field bytes (input and output) up to which the allocation-free operator entry point
+// takes a lattice.
+constexpr size_t kNoAllocBytes = (size_t)32 << 20;
 
 // A captured launch sequence and the key (list, sizes, buffers, launch shapes) it
 // was captured for.
@@ -165,7 +137,6 @@ struct tslov_ctx {
     int antiperiodic = 1, precision = TSLOV_FP64;
     hipStream_t st = nullptr;
     int device = 0;
-    char* scratch = nullptr;   // this device's scratch array (allocation-free operator)
     size_t lds_max = 65536;
     int links_set = 0;
     int diag = 0;    // tslov_set_diagnostics flags
@@ -178,7 +149,6 @@ struct tslov_ctx {
     Buf U64, U32;
     Buf badflag;     // device int: a non-finite link element was seen
     Buf sbmap;       // Geom::sbmap
-    Buf opf;         // two working-precision fields for the plain operator
     // batch workspace: per slot, kcap steps of v, w, a = Hv, b = H^dag w (and
     // abar, sbar for the derivative), kNF fields and kNP partial arrays
     Buf basisV, basisW, basisA, basisB, abarS, sbarS;
@@ -1677,10 +1647,10 @@ tslov_status deflated_grad(tslov_ctx* c, const ZD* eta, const ZD* psi, int k, co
 namespace {
 
 // Chunk length of the t-march operator, picked on the first call by timing each
-// candidate (best of three launches) on the call's own internal buffers: every
-// candidate gives the same result, so the pick changes the time only.
+// candidate (best of three launches) on the call's own arrays: every candidate writes
+// the same result, so the pick changes the time only.
 template <typename R, typename RL>
-tslov_status pick_apply_chunk(tslov_ctx* c, const Z<RL>* U, const Z<R>* a, Z<R>* b, double mu, int g5in, int g5out) {
+tslov_status pick_apply_chunk(tslov_ctx* c, const Z<RL>* U, const ZD* a, ZD* b, double mu, int g5in, int g5out) {
     if (c->tm_T != 0) return TSLOV_OK;
     int cand[16];
     const int n = tslov::tmarch_chunks(c->g, cand, 16);
@@ -1705,7 +1675,8 @@ tslov_status pick_apply_chunk(tslov_ctx* c, const Z<RL>* U, const Z<R>* a, Z<R>*
         for (int i = 0; i < n; ++i) {
             const size_t x = (size_t)2 * (r * n + i);
             (void)hipEventRecord(ev[x], c->st);
-            tslov::launch_apply<R, RL>(U, a, b, c->g, c->kappa, mu, g5in, g5out, c->st, tslov::Timing{}, cand[i]);
+            tslov::launch_apply_canonical<R, RL>(U, a, b, c->g, c->kappa, mu, g5in, g5out, c->st, tslov::Timing{},
+                                                 cand[i]);
             (void)hipEventRecord(ev[x + 1], c->st);
         }
     const hipError_t es = hipEventSynchronize(ev.back());
@@ -1727,24 +1698,17 @@ tslov_status pick_apply_chunk(tslov_ctx* c, const Z<RL>* U, const Z<R>* a, Z<R>*
     return TSLOV_OK;
 }
 
-// The operator on canonical spinors: to the context's field layout, the stencil,
-// and back.
-// staging: the two SoA fields (the context's workspace, or the scratch array of
-// the allocation-free entry point, which neither times launches nor picks the
-// marching chunk length by timing: it takes the context's pick if one was made,
-// else the built-in choice; every chunk length gives the same bits).
+// The operator on canonical spinors.  The allocation-free entry point neither times
+// launches nor picks the marching chunk length by timing: it takes the context's pick if
+// one was made, else the built-in choice (every chunk length gives the same bits).
 template <typename R, typename RL>
-tslov_status apply_fields(tslov_ctx* c, const void* in, void* out, double mu, int g5in, int g5out, void* staging,
-                          int no_alloc) {
-    Z<R>* a = static_cast<Z<R>*>(staging);
-    Z<R>* b = a + c->field_elems();
+tslov_status apply_fields(tslov_ctx* c, const void* in, void* out, double mu, int g5in, int g5out, int no_alloc) {
     const Z<RL>* U = links<RL>(c);
-    tslov::launch_spinor_to_soa<R>((const ZD*)in, a, c->g, nullptr, c->st);
-    if (!c->tm_T_forced && !no_alloc) CHK((pick_apply_chunk<R, RL>(c, U, a, b, mu, g5in, g5out)));
-    tslov::launch_apply<R, RL>(U, a, b, c->g, c->kappa, mu, g5in, g5out, c->st,
-                               no_alloc ? tslov::Timing{} : TimedLaunch(c, 2).t,
-                               c->tm_T_forced ? c->tm_T_forced : std::max(c->tm_T, 0));
-    tslov::launch_spinor_from_soa<R>(b, (ZD*)out, c->g, c->st);
+    if (!c->tm_T_forced && !no_alloc)
+        CHK((pick_apply_chunk<R, RL>(c, U, (const ZD*)in, (ZD*)out, mu, g5in, g5out)));
+    tslov::launch_apply_canonical<R, RL>(U, (const ZD*)in, (ZD*)out, c->g, c->kappa, mu, g5in, g5out, c->st,
+                                         no_alloc ? tslov::Timing{} : TimedLaunch(c, 2).t,
+                                         c->tm_T_forced ? c->tm_T_forced : std::max(c->tm_T, 0));
     return TSLOV_OK;
 }
 
@@ -2067,11 +2031,8 @@ tslov_status tslov_create(const tslov_lattice_desc* d, void* stream, tslov_ctx**
     HIPCHK(hipGetDevice(&dev));
     hipDeviceProp_t prop;
     HIPCHK(hipGetDeviceProperties(&prop, dev));
-    char* scr = nullptr;
-    CHK(scratch_address(dev, &scr));
     tslov_ctx* c = new tslov_ctx();
     c->device = dev;
-    c->scratch = scr;
     c->lds_max = prop.sharedMemPerBlock ? prop.sharedMemPerBlock : 65536;
     c->g.nx = d->dims[0];
     c->g.ny = d->dims[1];
@@ -2107,7 +2068,7 @@ tslov_status tslov_create(const tslov_lattice_desc* d, void* stream, tslov_ctx**
 void tslov_destroy(tslov_ctx* c) {
     if (!c) return;
     (void)hipStreamSynchronize(c->st);
-    for (Buf* b : {&c->trial, &c->solvebuf, &c->physbuf, &c->U64, &c->U32, &c->badflag, &c->nestbuf, &c->blk, &c->bdefl, &c->deflb, &c->curdefl, &c->sbmap, &c->opf, &c->basisV, &c->basisW, &c->basisA, &c->basisB, &c->abarS, &c->sbarS,
+    for (Buf* b : {&c->trial, &c->solvebuf, &c->physbuf, &c->U64, &c->U32, &c->badflag, &c->nestbuf, &c->blk, &c->bdefl, &c->deflb, &c->curdefl, &c->sbmap, &c->basisV, &c->basisW, &c->basisA, &c->basisB, &c->abarS, &c->sbarS,
                    &c->fields, &c->part, &c->coefmem, &c->dense, &c->rat, &c->denseInt, &c->densePart, &c->denseDelta,
                    &c->gpart, &c->gsrc, &c->bout, &c->wardp, &c->canon, &c->deflw, &c->deflx, &c->cgf, &c->cgp,
                    &c->cgs, &c->ckpt})
@@ -2144,23 +2105,14 @@ static tslov_status apply_op(tslov_ctx* c, const void* in, void* out, double mu,
     if (!c || !in || !out) return fail(TSLOV_ERR_ARG, "null argument");
     if (!c->links_set) return fail(TSLOV_ERR_ARG, "links not set (call tslov_set_links first)");
     if (in == out) return fail(TSLOV_ERR_ARG, "in and out must not overlap");
-    void* staging = nullptr;
-    if (no_alloc) {
-        if (2 * c->field_bytes() > kScratchBytes)
-            return fail(TSLOV_ERR_ARG, "lattice too large for the allocation-free operator (" +
-                                           std::to_string(2 * c->field_bytes()) + " bytes of staging, at most " +
-                                           std::to_string(kScratchBytes) + ")");
-        staging = c->scratch;
-    } else {
-        CHK(ensure(c->opf, 2 * c->field_bytes()));
-        staging = c->opf.p;
-    }
+    if (no_alloc && 2 * c->field_bytes() > kNoAllocBytes)
+        return fail(TSLOV_ERR_ARG, "lattice too large for the allocation-free operator (" +
+                                       std::to_string(2 * c->field_bytes()) + " bytes of fields, at most " +
+                                       std::to_string(kNoAllocBytes) + ")");
     switch (c->precision) {
-        case TSLOV_MIXED: CHK((apply_fields<float, float>(c, in, out, mu, g5in, g5out, staging, no_alloc))); break;
-        case TSLOV_FP32_LINKS:
-            CHK((apply_fields<double, float>(c, in, out, mu, g5in, g5out, staging, no_alloc)));
-            break;
-        default: CHK((apply_fields<double, double>(c, in, out, mu, g5in, g5out, staging, no_alloc)));
+        case TSLOV_MIXED: CHK((apply_fields<float, float>(c, in, out, mu, g5in, g5out, no_alloc))); break;
+        case TSLOV_FP32_LINKS: CHK((apply_fields<double, float>(c, in, out, mu, g5in, g5out, no_alloc))); break;
+        default: CHK((apply_fields<double, double>(c, in, out, mu, g5in, g5out, no_alloc)));
     }
     HIPCHK(hipGetLastError());
     return TSLOV_OK;
@@ -2751,7 +2703,7 @@ double tslov_kernel_bytes(const tslov_ctx* c, int which) {
     switch (which) {
         case 0: return V * (6 * 12 * z + 36 * zl);      // read r, s, links; write v, w, a, b
         case 1: return V * (12 * 12 * z + 36 * zl);     // read 9 fields and links; write 3 fields
-        case 2: return V * (2 * 12 * z + 36 * zl);      // read in and links; write out
+        case 2: return V * (2 * 12 * sizeof(ZD) + 36 * zl);   // read in and links; write out (canonical)
         default: return 0.0;
     }
 }

@@ -701,6 +701,277 @@ void launch_apply(const Z<RL>* U, const Z<R>* in, Z<R>* out, const Geom& g, doub
     }
 }
 
+// =============================================================== operator on canonical spinors
+// out = g5^{g5_out} (x - kappa hop x'), x' = g5^{g5_in} in, straight from the caller's
+// canonical array to the caller's canonical array.  A block of four wavefronts owns 64
+// consecutive sites, wavefront nu both hops of direction nu for every colour, so a site's
+// 108 neighbour and link loads are in flight at once; the link-applied half spinors meet
+// in LDS, where one wavefront per colour adds the eight hops in the fixed order (x, y, z,
+// t; forward, backward) and applies the epilogue.  Neighbour spinors are gathered in
+// runs: four lanes read 64 contiguous bytes of one site, and LDS rows of 13 elements
+// (208 bytes, conflict-free for the 16-byte reads) turn them into one site per lane; the
+// result leaves as one contiguous run.
+// march: the block walks T consecutive t-slices of its (x, y, z) tile.  psi(t+1), staged
+// for the forward t-hop, is the own spinor of the next slice, and U_t(t)^dag P- psi(t), the
+// next slice's backward t-hop before reconstruction, is carried in registers, so along t
+// every spinor and link is read once per chunk (the first slice of a chunk forms its
+// backward hop with the same arithmetic: the bits do not depend on T).  Tiles and chunks
+// go out so that each XCD takes the same run of tiles, a slab of z-planes, in every chunk.
+// Bound: memory on large lattices (two blocks per compute unit, by LDS), one round trip and
+// two barriers on small ones.  Measured per call against the three launches it replaces
+// (canonical to planes, stencil on planes, planes to canonical): 32^4 float64 250 us (1.007
+// GB algorithmic, 4.0 TB/s) against 421, 18^3x6 float32 11.0 us against 20.0, 8^4 float64
+// 6.3 us against 12.4.  Chunks of 1, 2, 4, 8, 16 and 32 slices at 32^4: 273, 275, 256, 250,
+// 256 and 266 us; at 16^4, where a march leaves compute units idle, 16, 16, 20 and 30 us for
+// 1, 2, 4 and 8, so the length is picked by timing (pick_apply_chunk).
+constexpr int kSlot = 13;        // LDS elements per site
+constexpr int kDirBlock = 4 * kSites;
+
+template <typename R>
+using SpinorTile = Z<R>[kSites * kSlot];
+
+// Elements that lane l reads of a gather of 64 sites: site (l / 4) + 16 q, spin-colour
+// elements (l % 4) + 4 c.
+template <typename R>
+struct Gather {
+    Z<R> v[12];
+};
+
+template <typename R>
+__device__ __forceinline__ void gather_load(Gather<R>& gt, const ZD* __restrict__ in, int site) {
+    const int l = threadIdx.x % kWave;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const ZD* const p = in + (size_t)__shfl(site, (l >> 2) + 16 * q) * 12 + (l & 3);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) gt.v[3 * q + c] = zcast<R>(p[4 * c]);
+    }
+}
+
+template <typename R>
+__device__ __forceinline__ void gather_stage(SpinorTile<R>& t, const Gather<R>& gt) {
+    const int l = threadIdx.x % kWave;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) t[((l >> 2) + 16 * q) * kSlot + (l & 3) + 4 * c] = gt.v[3 * q + c];
+}
+
+// Order LDS accesses between the lanes of one wavefront.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+template <typename R>
+__device__ __forceinline__ void tile_spinor(Spinor<R>& p, const SpinorTile<R>& t, int g5) {
+    const int l = threadIdx.x % kWave;
+#pragma unroll
+    for (int e = 0; e < 12; ++e) p.c[e / 3][e % 3] = t[l * kSlot + e];
+    if (g5) g5_inplace(p);
+}
+
+// Forms of the link products: the colour grid's lattices, the others site by site, and the
+// marching ones.
+constexpr int kLinkRow = 0, kLinkSite = 1, kLinkMarch = 2;
+
+// o = M h with M = U (DIR > 0) or U^dag (DIR < 0).  kLinkRow: row_dot's chain.  Else a sum of
+// three products, one half of each part fused; which half is fixed here per form and
+// direction (in float32 the choice moves the last bit, and a lattice's results are to keep
+// their bits whatever kernel or compiler forms them).
+template <int NU, int DIR, int FORM, typename R>
+__device__ __forceinline__ void link_apply(Z<R> (&o)[2][3], const Z<R> (&u)[3][3], const Z<R> (&h)[2][3]) {
+    constexpr bool odd = NU % 2 == 1;
+    constexpr bool swap_im = DIR > 0 && (FORM == kLinkMarch ? odd : !odd);
+    constexpr bool swap_re = DIR < 0 && odd;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        Z<R> m[3];
+#pragma unroll
+        for (int b = 0; b < 3; ++b) m[b] = DIR > 0 ? u[a][b] : cj(u[b][a]);
+#pragma unroll
+        for (int sp = 0; sp < 2; ++sp) {
+            if (FORM == kLinkRow) {
+                o[sp][a] = row_dot(m, h[sp][0], h[sp][1], h[sp][2]);
+                continue;
+            }
+            Z<R> t[3];
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const Z<R> x = h[sp][b];
+                t[b].re = swap_re ? fmadd(-m[b].im, x.im, m[b].re * x.re) : fmadd(m[b].re, x.re, -(m[b].im * x.im));
+                t[b].im = swap_im ? fmadd(m[b].im, x.re, m[b].re * x.im) : fmadd(m[b].re, x.im, m[b].im * x.re);
+            }
+            o[sp][a] = t[0] + t[1] + t[2];
+        }
+    }
+}
+
+template <typename R>
+__device__ __forceinline__ void put_half(SpinorTile<R>& t, int hop, const Z<R> (&o)[2][3]) {
+    const int l = threadIdx.x % kWave;
+#pragma unroll
+    for (int sp = 0; sp < 2; ++sp)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) t[((hop * 2 + sp) * 3 + c) * kSites + l] = o[sp][c];
+}
+
+// Both hops of direction NU: gather, project, link, result into the wavefront's tile.
+template <int NU, int FORM, typename R, typename RL>
+__device__ __forceinline__ void dir_hops(SpinorTile<R>& t, const Z<RL>* __restrict__ U, const ZD* __restrict__ in,
+                                         const Geom& g, int s, int yf, int yb, int g5_in) {
+    Gather<R> gf, gb;
+    Z<R> uf[3][3], ub[3][3];
+    gather_load(gf, in, yf);
+    gather_load(gb, in, yb);
+    load_link(uf, U, g.ldv, NU, s);
+    load_link(ub, U, g.ldv, NU, yb);
+    mem_fence_compiler();
+    Spinor<R> p;
+    Z<R> h[2][3], of[2][3], ob[2][3];
+    gather_stage(t, gf);
+    wave_lds_fence();
+    tile_spinor(p, t, g5_in);
+    project<NU, +1>(p, h);
+    link_apply<NU, +1, FORM>(of, uf, h);
+    wave_lds_fence();
+    gather_stage(t, gb);
+    wave_lds_fence();
+    tile_spinor(p, t, g5_in);
+    project<NU, -1>(p, h);
+    link_apply<NU, -1, FORM>(ob, ub, h);
+    wave_lds_fence();
+    put_half(t, 0, of);
+    put_half(t, 1, ob);
+}
+
+template <int NU, typename R>
+__device__ __forceinline__ void add_hops(Z<R> (&acc)[4], const SpinorTile<R>& t, int a, int l, R cf, R cb) {
+    const Z<R> of[2] = {t[a * kSites + l], t[(3 + a) * kSites + l]};
+    const Z<R> ob[2] = {t[(6 + a) * kSites + l], t[(9 + a) * kSites + l]};
+    recon1_add<NU, +1>(acc, of, cf);
+    recon1_add<NU, -1>(acc, ob, cb);
+}
+
+template <typename R, typename RL, int FORM>
+__global__ __launch_bounds__(kDirBlock) void k_apply_dirs(const Z<RL>* __restrict__ U, const ZD* __restrict__ in,
+                                                          ZD* __restrict__ out, Geom g, R kappa, R ep, R em,
+                                                          int g5_in, int g5_out, int T) {
+    constexpr bool march = FORM == kLinkMarch;
+    __shared__ SpinorTile<R> hops[4];
+    __shared__ SpinorTile<R> own[2];
+    const int V3 = g.nx * g.ny * g.nz;
+    const int nu = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kSites), l = threadIdx.x % kSites;
+    int s0, t0 = 0;   // first site of the block, first slice
+    if (march) {
+        const int per = V3 / kSites / kXcd, m = blockIdx.x / kXcd;
+        t0 = m / per * T;
+        s0 = ((blockIdx.x % kXcd) * per + m % per) * kSites + t0 * V3;
+    } else {
+        s0 = xcd_block(blockIdx.x, gridDim.x) * kSites;
+        if (s0 >= g.V) return;   // padding block
+    }
+    const int sl = min(s0 + l, g.V - 1);
+    const Nbr n = neighbours(g, sl);
+    const int nf = nu == 0 ? n.fwd[0] : nu == 1 ? n.fwd[1] : nu == 2 ? n.fwd[2] : n.fwd[3];
+    const int nb = nu == 0 ? n.bwd[0] : nu == 1 ? n.bwd[1] : nu == 2 ? n.bwd[2] : n.bwd[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {   // the first slice's own spinors, one contiguous run
+        const int f = threadIdx.x + i * kDirBlock;
+        own[0][f / 12 * kSlot + f % 12] = zcast<R>(in[min((size_t)s0 * 12 + f, (size_t)12 * g.V - 1)]);
+    }
+    if (T > 1) __syncthreads();     // wavefront 3 reads them before the hops' barrier
+    Z<R> carry[2][3];               // wavefront 3: the next slice's backward t-hop
+    for (int i = 0; i < T; ++i) {
+        SpinorTile<R>& cur = own[i & 1];
+        const int d = i * V3, s = sl + d;
+        if (nu == 0) dir_hops<0, FORM>(hops[0], U, in, g, s, nf + d, nb + d, g5_in);
+        else if (nu == 1) dir_hops<1, FORM>(hops[1], U, in, g, s, nf + d, nb + d, g5_in);
+        else if (nu == 2) dir_hops<2, FORM>(hops[2], U, in, g, s, nf + d, nb + d, g5_in);
+        else if (T == 1) dir_hops<3, FORM>(hops[3], U, in, g, s, nf, nb, g5_in);
+        else {
+            SpinorTile<R>& nxt = own[(i & 1) ^ 1];
+            Gather<R> gf;
+            Z<R> u[3][3], h[2][3], of[2][3];
+            Spinor<R> p;
+            gather_load(gf, in, t0 + i + 1 == g.nt ? s - (g.nt - 1) * V3 : s + V3);
+            load_link(u, U, g.ldv, 3, s);
+            if (i == 0) {
+                Gather<R> gb;
+                Z<R> ub[3][3];
+                gather_load(gb, in, nb);
+                load_link(ub, U, g.ldv, 3, nb);
+                mem_fence_compiler();
+                gather_stage(hops[3], gb);
+                wave_lds_fence();
+                tile_spinor(p, hops[3], g5_in);
+                project<3, -1>(p, h);
+                link_apply<3, -1, FORM>(carry, ub, h);
+                wave_lds_fence();
+            }
+            mem_fence_compiler();
+            put_half(hops[3], 1, carry);
+            gather_stage(nxt, gf);
+            wave_lds_fence();
+            tile_spinor(p, nxt, g5_in);
+            project<3, +1>(p, h);
+            link_apply<3, +1, FORM>(of, u, h);
+            put_half(hops[3], 0, of);
+            tile_spinor(p, cur, g5_in);
+            project<3, -1>(p, h);
+            link_apply<3, -1, FORM>(carry, u, h);
+        }
+        __syncthreads();
+        if (nu < 3) {   // colour nu: the hop sum and the epilogue, in place of the own spinor
+            Z<R> acc[4];
+            zero1(acc);
+            add_hops<0>(acc, hops[0], nu, l, R(1), R(1));
+            add_hops<1>(acc, hops[1], nu, l, R(1), R(1));
+            add_hops<2>(acc, hops[2], nu, l, R(1), R(1));
+            add_hops<3>(acc, hops[3], nu, l, ep, em);
+#pragma unroll
+            for (int sp = 0; sp < 4; ++sp) {
+                const R s_in = (g5_in && sp >= 2) ? R(-1) : R(1);
+                const R s_out = (g5_out && sp >= 2) ? R(-1) : R(1);
+                Z<R>& x = cur[l * kSlot + sp * 3 + nu];
+                x = s_out * (s_in * x - kappa * acc[sp]);
+            }
+        }
+        __syncthreads();
+        const size_t o = (size_t)(s0 + d) * 12;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int f = threadIdx.x + k * kDirBlock;
+            if (o + f < (size_t)12 * g.V) {
+                const ZD y = zcast<double>(cur[f / 12 * kSlot + f % 12]);
+                double* q = reinterpret_cast<double*>(out + o + f);
+                __builtin_nontemporal_store(y.re, q);
+                __builtin_nontemporal_store(y.im, q + 1);
+            }
+        }
+        if (i + 1 < T) __syncthreads();   // the next slice stages into this tile
+    }
+}
+
+// The march takes lattices whose (x, y, z) tiles split evenly over the XCDs.
+template <typename R, typename RL>
+void launch_apply_canonical(const Z<RL>* U, const ZD* in, ZD* out, const Geom& g, double kappa, double mu, int g5_in,
+                            int g5_out, hipStream_t st, Timing t, int tm_T) {
+    const R ep = (R)std::exp(mu), em = (R)std::exp(-mu);
+    auto go = [&](auto kernel, int nb, int T) {
+        timed_launch(kernel, dim3(nb), dim3(kDirBlock), st, t, U, in, out, g, (R)kappa, ep, em, g5_in, g5_out, T);
+    };
+    const int chunk = colour_grid(g.V) ? 0 : tmarch_chunk(g);
+    if (chunk) {
+        const int T = tm_T > 0 && g.nt % tm_T == 0 ? tm_T : chunk;
+        go(k_apply_dirs<R, RL, kLinkMarch>, g.nx * g.ny * g.nz / kSites * (g.nt / T), T);
+    } else if (colour_grid(g.V)) {
+        go(k_apply_dirs<R, RL, kLinkRow>, nsb_pad(g.V), 1);
+    } else {
+        go(k_apply_dirs<R, RL, kLinkSite>, nsb_pad(g.V), 1);
+    }
+}
+
 // =============================================================== batched sources
 // Grid dimension y (or z) runs over the entries of a SrcList; the entry's slot
 // selects its workspace and coefficients.
@@ -2028,6 +2299,8 @@ int launch_biorth(const Geom& g, const Work<R>& wk, const SrcList& L, Coef coef,
 #define TSLOV_INST_STENCIL(R, RL)                                                                               \
     template void launch_apply<R, RL>(const Z<RL>*, const Z<R>*, Z<R>*, const Geom&, double, double, int, int,  \
                                       hipStream_t, Timing, int);                                                \
+    template void launch_apply_canonical<R, RL>(const Z<RL>*, const ZD*, ZD*, const Geom&, double, double, int, \
+                                                int, hipStream_t, Timing, int);                                 \
     template void launch_fwd_pair<R, RL>(const Z<RL>*, const Geom&, double, double, const Work<R>&,             \
                                          const SrcList&, Coef, int, int, int, hipStream_t, Timing);             \
     template void launch_fwd_replay<R, RL>(const Z<RL>*, const Geom&, double, double, const Work<R>&,           \

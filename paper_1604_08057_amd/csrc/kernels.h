@@ -28,6 +28,10 @@ void launch_spinor_from_soa(const Z<R>* in, ZD* out, const Geom& g, hipStream_t 
 template <typename R, typename RL>
 void launch_apply(const Z<RL>* U, const Z<R>* in, Z<R>* out, const Geom& g, double kappa, double mu,
                   int g5_in, int g5_out, hipStream_t st, Timing t = {}, int tm_T = 0);
+// The same on canonical spinors (float64 complex, caller's arrays), fields rounded to R.
+template <typename R, typename RL>
+void launch_apply_canonical(const Z<RL>* U, const ZD* in, ZD* out, const Geom& g, double kappa, double mu, int g5_in,
+                            int g5_out, hipStream_t st, Timing t = {}, int tm_T = 0);
 // The t-slices per chunk the t-march operator can run this lattice with (each
 // gives the same result), at most maxn of them into T; 0 when it does not apply.
 // launch_apply's tm_T picks one (0: the built-in choice).
