@@ -948,37 +948,36 @@ tslov_status block_tsl(tslov_ctx* c, const tslov::BlockTangent& t, const ZD* x1,
                        ZD* y2, EntryStatus& es) {
     const Geom& g = c->g;
     const size_t fe = c->field_elems();
-    const int nb = tslov::blk_blocks(g);
-    CHK(ensure(c->blk, ((size_t)14 + 2 * (size_t)k) * fe * sizeof(ZD) + (size_t)8 * nb * sizeof(double)));
+    CHK(ensure(c->blk, ((size_t)14 + 2 * (size_t)k) * fe * sizeof(ZD)));
+    CHK(ensure_work(c, 1, k, 0));   // coefficients and partial sums
+    const Work<double> wk = work<double>(c);
     tslov::BlockFields f;
     ZD* base = c->blk.as<ZD>();
     for (int h = 0; h < 2; ++h) {
         f.x[h] = base + (0 + h) * fe;
-        f.v[h] = base + (2 + h) * fe;
-        f.w[h] = base + (4 + h) * fe;
-        f.vp[h] = base + (6 + h) * fe;
-        f.wp[h] = base + (8 + h) * fe;
-        f.a[h] = base + (10 + h) * fe;
-        f.b[h] = base + (12 + h) * fe;
+        f.r[h] = base + (2 + h) * fe;
+        f.s[h] = base + (4 + h) * fe;
+        f.a[h] = base + (6 + h) * fe;
+        f.b[h] = base + (8 + h) * fe;
+        f.w[h][0] = base + (10 + h) * fe;
+        f.w[h][1] = base + (12 + h) * fe;
         f.basis[h] = base + (14 + (size_t)h * k) * fe;
+        f.pair[h] = wk.p(0, h);
+        f.recur[h] = wk.p(0, 2 + h);
     }
-    double* p0 = (double*)(base + (14 + 2 * (size_t)k) * fe);
-    double* p1 = p0 + 4 * nb;
-    CHK(ensure_work(c, 1, k, 0));
-    if (x1) tslov::launch_spinor_to_soa<double>(x1, f.x[0], g, nullptr, c->st);
-    else tslov::launch_zero((double*)f.x[0], 2 * fe, c->st);
-    tslov::launch_spinor_to_soa<double>(x2, f.x[1], g, nullptr, c->st);
+    if (x1) {
+        tslov::launch_spinor_to_soa<double>(x1, f.x[0], g, f.recur[0], c->st);
+    } else {
+        tslov::launch_zero((double*)f.x[0], 2 * fe, c->st);
+        tslov::launch_zero(f.recur[0], (size_t)tslov::kNvRecur * tslov::grid_for(g.V), c->st);
+    }
+    tslov::launch_spinor_to_soa<double>(x2, f.x[1], g, f.recur[1], c->st);
     std::vector<int> init(16, 0);
+    init[1] = k;
     HIPCHK(hipMemcpyAsync(c->coef.status, init.data(), init.size() * sizeof(int), hipMemcpyHostToDevice, c->st));
-    tslov::launch_blk_start(f, g, c->coef, p0, c->st);
-    const ZD* U = c->U64.as<ZD>();
     for (int j = 1; j <= k; ++j) {
-        tslov::launch_apply<double, double>(U, f.v[0], f.a[0], g, c->kappa, c->mu, 0, 1, c->st);
-        tslov::launch_apply<double, double>(U, f.v[1], f.a[1], g, c->kappa, c->mu, 0, 1, c->st);
-        tslov::launch_apply<double, double>(U, f.w[0], f.b[0], g, c->kappa, -c->mu, 0, 1, c->st);
-        tslov::launch_apply<double, double>(U, f.w[1], f.b[1], g, c->kappa, -c->mu, 0, 1, c->st);
-        tslov::launch_blk_tangent(U, t, g, c->kappa, c->mu, f.v[1], f.a[0], f.w[0], f.b[1], c->st);
-        tslov::launch_blk_step(f, g, c->coef, p0, p1, j, k, c->st);
+        tslov::launch_blk_pair(c->U64.as<ZD>(), t, f, g, c->kappa, c->mu, c->coef, j, c->st);
+        tslov::launch_blk_recur(f, g, c->coef, j, k, c->st);
     }
     HIPCHK(hipGetLastError());
     int st[16];
@@ -1675,7 +1674,7 @@ tslov_status pick_apply_chunk(tslov_ctx* c, const Z<RL>* U, const ZD* a, ZD* b, 
         for (int i = 0; i < n; ++i) {
             const size_t x = (size_t)2 * (r * n + i);
             (void)hipEventRecord(ev[x], c->st);
-            tslov::launch_apply_canonical<R, RL>(U, a, b, c->g, c->kappa, mu, g5in, g5out, c->st, tslov::Timing{},
+            tslov::launch_apply<R, RL>(U, a, b, c->g, c->kappa, mu, g5in, g5out, c->st, tslov::Timing{},
                                                  cand[i]);
             (void)hipEventRecord(ev[x + 1], c->st);
         }
@@ -1706,7 +1705,7 @@ tslov_status apply_fields(tslov_ctx* c, const void* in, void* out, double mu, in
     const Z<RL>* U = links<RL>(c);
     if (!c->tm_T_forced && !no_alloc)
         CHK((pick_apply_chunk<R, RL>(c, U, (const ZD*)in, (ZD*)out, mu, g5in, g5out)));
-    tslov::launch_apply_canonical<R, RL>(U, (const ZD*)in, (ZD*)out, c->g, c->kappa, mu, g5in, g5out, c->st,
+    tslov::launch_apply<R, RL>(U, (const ZD*)in, (ZD*)out, c->g, c->kappa, mu, g5in, g5out, c->st,
                                          no_alloc ? tslov::Timing{} : TimedLaunch(c, 2).t,
                                          c->tm_T_forced ? c->tm_T_forced : std::max(c->tm_T, 0));
     return TSLOV_OK;

@@ -21,43 +21,6 @@ void timed_launch(K kernel, dim3 grid, dim3 block, hipStream_t st, Timing t, Arg
 // being hoisted above the hopping loop, where they would stay live (and spill).
 __device__ __forceinline__ void mem_fence_compiler() { asm volatile("" ::: "memory"); }
 
-// One direction of the hopping sum for a single field.
-template <int NU, typename R, typename RL>
-__device__ __forceinline__ void hop_dir(Spinor<R>& acc, const Z<RL>* __restrict__ U, const Z<R>* __restrict__ in,
-                                        const Geom& g, int s, const Nbr& n, R cf, R cb, int g5_in) {
-    Z<R> u[3][3];
-    Spinor<R> p;
-    load_link(u, U, g.ldv, NU, s);
-    load_spinor(p, in, g.ldv, n.fwd[NU]);
-    if (g5_in) g5_inplace(p);
-    hop_fwd<NU>(acc, u, p, cf);
-    load_link(u, U, g.ldv, NU, n.bwd[NU]);
-    load_spinor(p, in, g.ldv, n.bwd[NU]);
-    if (g5_in) g5_inplace(p);
-    hop_bwd<NU>(acc, u, p, cb);
-}
-
-// One direction of the hopping sums of two fields sharing the link loads:
-// field A with chemical potential +mu, field B with -mu.
-template <int NU, typename R, typename RL>
-__device__ __forceinline__ void hop_dir_pair(Spinor<R>& acca, Spinor<R>& accb, const Z<RL>* __restrict__ U,
-                                             const Z<R>* __restrict__ fa, const Z<R>* __restrict__ fb,
-                                             const Geom& g, int s, const Nbr& n, R ep, R em) {
-    const R fa_f = (NU == 3) ? ep : R(1), fa_b = (NU == 3) ? em : R(1);
-    Z<R> u[3][3];
-    Spinor<R> p;
-    load_link(u, U, g.ldv, NU, s);
-    load_spinor(p, fa, g.ldv, n.fwd[NU]);
-    hop_fwd<NU>(acca, u, p, fa_f);
-    load_spinor(p, fb, g.ldv, n.fwd[NU]);
-    hop_fwd<NU>(accb, u, p, fa_b);
-    load_link(u, U, g.ldv, NU, n.bwd[NU]);
-    load_spinor(p, fa, g.ldv, n.bwd[NU]);
-    hop_bwd<NU>(acca, u, p, fa_b);
-    load_spinor(p, fb, g.ldv, n.bwd[NU]);
-    hop_bwd<NU>(accb, u, p, fa_f);
-}
-
 }  // namespace
 
 // =============================================================== layout
@@ -135,8 +98,7 @@ void launch_spinor_from_soa(const Z<R>* in, ZD* out, const Geom& g, hipStream_t 
 // lattices): single-wavefront blocks, block (a, b) handles colour a of site block b,
 // which spreads the three colours of a site over three compute units.  Colour split
 // (the Lanczos pair kernels on larger lattices): blocks of 3 wavefronts, wavefront a
-// handles colour a.  The operator on larger lattices uses one thread per site
-// (k_apply_site).
+// handles colour a.  The operator alone has its own layout (k_apply_dirs).
 template <typename R>
 __device__ __forceinline__ void load1(Z<R> (&p)[4], const Z<R>* __restrict__ f, int ldv, int a, int s) {
 #pragma unroll
@@ -186,32 +148,6 @@ __device__ __forceinline__ void hop_dir_pair1(Z<R> (&acca)[4], Z<R> (&accb)[4], 
     hop1<NU, -1>(acca, u, p, dn);
     load_spinor(p, fb, g.ldv, n.bwd[NU]);
     hop1<NU, -1>(accb, u, p, up);
-}
-
-// Both hops of direction NU for one field (colour a):
-//   acc += cf (1+g) U(x) f(x+nu) + cb (1-g) U(x-nu)^dag f(x-nu), f optionally g5-multiplied,
-// with every load of the direction issued before any arithmetic (the compiler
-// barrier keeps the scheduler from sinking the loads to their uses): one memory
-// round trip per direction instead of one per loaded operand, at the cost of
-// holding all operands of a direction in registers.  The pair version below does
-// the same for two fields sharing the link rows.
-template <int NU, typename R, typename RL>
-__device__ __forceinline__ void hop_dir1_eager(Z<R> (&acc)[4], const Z<RL>* __restrict__ U,
-                                               const Z<R>* __restrict__ f, const Geom& g, int s, int a, const Nbr& n,
-                                               R cf, R cb, int g5_in) {
-    Z<R> uf[3], ub[3];
-    Spinor<R> pf, pb;
-    load_row(uf, U, g.ldv, NU, a, s);
-    load_spinor(pf, f, g.ldv, n.fwd[NU]);
-    load_col_conj(ub, U, g.ldv, NU, a, n.bwd[NU]);
-    load_spinor(pb, f, g.ldv, n.bwd[NU]);
-    mem_fence_compiler();
-    if (g5_in) {
-        g5_inplace(pf);
-        g5_inplace(pb);
-    }
-    hop1<NU, +1>(acc, uf, pf, cf);
-    hop1<NU, -1>(acc, ub, pb, cb);
 }
 
 // All eight hops of two fields (colour a) sharing the link rows (A at +mu, B at
@@ -407,262 +343,9 @@ __device__ __forceinline__ unsigned block_live(const Coef& coef0, const SrcList&
 }
 
 // =============================================================== operator
-// Colour grid (small lattices): block (a, b) forms colour a of site block b.
-template <typename R, typename RL>
-__global__ __launch_bounds__(kSites) void k_apply(const Z<RL>* __restrict__ U, const Z<R>* __restrict__ in,
-                                                  Z<R>* __restrict__ out, Geom g, R kappa, R ep, R em, int g5_in,
-                                                  int g5_out) {
-    const int a = sten_colour<kSites>();
-    const int s = sten_block<kSites>(g) * kSites + threadIdx.x;
-    if (s >= g.V) return;
-    const Nbr n = neighbours(g, s);
-    Z<R> acc[4];
-    zero1(acc);
-#pragma unroll 1
-    for (int nu = 0; nu < 4; ++nu) {
-        switch (nu) {
-            case 0: hop_dir1_eager<0>(acc, U, in, g, s, a, n, R(1), R(1), g5_in); break;
-            case 1: hop_dir1_eager<1>(acc, U, in, g, s, a, n, R(1), R(1), g5_in); break;
-            case 2: hop_dir1_eager<2>(acc, U, in, g, s, a, n, R(1), R(1), g5_in); break;
-            default: hop_dir1_eager<3>(acc, U, in, g, s, a, n, ep, em, g5_in); break;
-        }
-    }
-    mem_fence_compiler();
-    Z<R> x[4];
-    load1(x, in, g.ldv, a, s);
-#pragma unroll
-    for (int sp = 0; sp < 4; ++sp) {
-        const R s_in = (g5_in && sp >= 2) ? R(-1) : R(1);
-        const R s_out = (g5_out && sp >= 2) ? R(-1) : R(1);
-        x[sp] = s_out * (s_in * x[sp] - kappa * acc[sp]);
-    }
-    store1(out, g.ldv, a, s, x);
-}
-
-// Site per thread (lattices above the colour grid's range): each thread forms all
-// three colours of its site, so every neighbour spinor and link passes through the
-// compute unit's L1 once per site instead of once per colour wavefront.  Blocks go
-// out in XCD order: when the site blocks of a t-slice split evenly over the XCDs,
-// each XCD takes the same run of them in every slice, slice after slice, so that a
-// site's t-neighbours were read one run earlier on the same L2; otherwise each
-// XCD takes a contiguous run of the lattice.
-template <typename R, typename RL>
-__global__ __launch_bounds__(kBlock) void k_apply_site(const Z<RL>* __restrict__ U, const Z<R>* __restrict__ in,
-                                                       Z<R>* __restrict__ out, Geom g, R kappa, R ep, R em,
-                                                       int g5_in, int g5_out, int slice_order) {
-    int sb;
-    if (slice_order) {
-        // each XCD takes the same run of site blocks in every t-slice, t outermost:
-        // a site's t-neighbours were touched one slice's run earlier on this XCD
-        const int n3 = g.nx * g.ny * g.nz / kBlock, per = n3 / kXcd, m = blockIdx.x / kXcd;
-        sb = (m / per) * n3 + (blockIdx.x % kXcd) * per + m % per;
-    } else {
-        sb = xcd_block(blockIdx.x, gridDim.x);
-    }
-    const int s = sb * kBlock + threadIdx.x;
-    if (s >= g.V) return;
-    const Nbr n = neighbours(g, s);
-    Spinor<R> acc;
-#pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) acc.c[sp][c] = mk<R>(0, 0);
-#pragma unroll 1
-    for (int nu = 0; nu < 4; ++nu) {
-        Z<R> u[3][3];
-        Spinor<R> p;
-        switch (nu) {
-            case 0:
-                load_link(u, U, g.ldv, 0, s); load_spinor(p, in, g.ldv, n.fwd[0]); if (g5_in) g5_inplace(p);
-                hop_fwd<0>(acc, u, p, R(1));
-                load_link(u, U, g.ldv, 0, n.bwd[0]); load_spinor(p, in, g.ldv, n.bwd[0]); if (g5_in) g5_inplace(p);
-                hop_bwd<0>(acc, u, p, R(1));
-                break;
-            case 1:
-                load_link(u, U, g.ldv, 1, s); load_spinor(p, in, g.ldv, n.fwd[1]); if (g5_in) g5_inplace(p);
-                hop_fwd<1>(acc, u, p, R(1));
-                load_link(u, U, g.ldv, 1, n.bwd[1]); load_spinor(p, in, g.ldv, n.bwd[1]); if (g5_in) g5_inplace(p);
-                hop_bwd<1>(acc, u, p, R(1));
-                break;
-            case 2:
-                load_link(u, U, g.ldv, 2, s); load_spinor(p, in, g.ldv, n.fwd[2]); if (g5_in) g5_inplace(p);
-                hop_fwd<2>(acc, u, p, R(1));
-                load_link(u, U, g.ldv, 2, n.bwd[2]); load_spinor(p, in, g.ldv, n.bwd[2]); if (g5_in) g5_inplace(p);
-                hop_bwd<2>(acc, u, p, R(1));
-                break;
-            default:
-                load_link(u, U, g.ldv, 3, s); load_spinor(p, in, g.ldv, n.fwd[3]); if (g5_in) g5_inplace(p);
-                hop_fwd<3>(acc, u, p, ep);
-                load_link(u, U, g.ldv, 3, n.bwd[3]); load_spinor(p, in, g.ldv, n.bwd[3]); if (g5_in) g5_inplace(p);
-                hop_bwd<3>(acc, u, p, em);
-                break;
-        }
-    }
-    mem_fence_compiler();
-    Spinor<R> x;
-    load_spinor(x, in, g.ldv, s);
-#pragma unroll
-    for (int sp = 0; sp < 4; ++sp) {
-        const R s_in = (g5_in && sp >= 2) ? R(-1) : R(1);
-        const R s_out = (g5_out && sp >= 2) ? R(-1) : R(1);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) x.c[sp][c] = s_out * (s_in * x.c[sp][c] - kappa * acc.c[sp][c]);
-    }
-    // streaming stores: the result is not read again here and would only displace
-    // neighbour spinors and links from L2
-#pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            R* q = reinterpret_cast<R*>(out + (size_t)(sp * 3 + c) * g.ldv + s);
-            __builtin_nontemporal_store(x.c[sp][c].re, q);
-            __builtin_nontemporal_store(x.c[sp][c].im, q + 1);
-        }
-}
-
-// Both hops of direction NU for a whole site, with the four operands' loads
-// issued before any arithmetic (one memory round trip per direction).
-template <int NU, typename R, typename RL>
-__device__ __forceinline__ void tm_hops_eager(Spinor<R>& acc, const Z<RL>* __restrict__ U, const Z<R>* __restrict__ in,
-                                              const Geom& g, int s, int sf, int sb, int g5_in) {
-    Z<R> uf[3][3], ub[3][3];
-    Spinor<R> pf, pb;
-    load_link(uf, U, g.ldv, NU, s);
-    load_spinor(pf, in, g.ldv, sf);
-    load_link(ub, U, g.ldv, NU, sb);
-    load_spinor(pb, in, g.ldv, sb);
-    mem_fence_compiler();
-    if (g5_in) {
-        g5_inplace(pf);
-        g5_inplace(pb);
-    }
-    hop_fwd<NU>(acc, uf, pf, R(1));
-    hop_bwd<NU>(acc, ub, pb, R(1));
-}
-
-// Site per thread with a march along t: a thread owns one (x, y, z) site of a
-// 128-site tile and runs through a chunk of T consecutive t-slices.  The forward
-// t-hop's operands at slice t, psi(t+1) and U_t(t), are loaded once: psi(t+1) is
-// the own spinor of slice t+1, and U_t(t)^dag P- psi(t) (the backward t-hop of
-// slice t+1 before reconstruction) is carried in registers.  So along t every
-// spinor and link is read once per chunk instead of up to three times.  The hop
-// sum runs in the same order as k_apply_site (x, y, z, t; forward then backward),
-// with the same operations, so the two kernels give identical results.  Block
-// b works on tile (b mod 8) * per + (b / 8) mod per of chunk b / (8 per): each XCD
-// takes the same run of tiles (a slab of z-planes) in every chunk.
-template <typename R, typename RL>
-__global__ __launch_bounds__(kBlock) void k_apply_tmarch(const Z<RL>* __restrict__ U, const Z<R>* __restrict__ in,
-                                                         Z<R>* __restrict__ out, Geom g, R kappa, R ep, R em,
-                                                         int g5_in, int g5_out, int T) {
-    const int V3 = g.nx * g.ny * g.nz, per = V3 / kBlock / kXcd, m = blockIdx.x / kXcd;
-    const int tile = (blockIdx.x % kXcd) * per + m % per, chunk = m / per;
-    const int s3 = tile * kBlock + threadIdx.x;   // the (x, y, z) site; t = 0
-    const int t0 = chunk * T;
-    const Nbr n3 = neighbours(g, s3);
-    const R s_in_lo = R(1), s_in_hi = g5_in ? R(-1) : R(1), s_out_hi = g5_out ? R(-1) : R(1);
-    // the own spinor waits in a slot of LDS private to the thread (it is needed
-    // only after the x, y, z hops, whose operands take the registers)
-    __shared__ Z<R> stash[12][kBlock];
-    __shared__ Z<R> hstash[6][kBlock];
-    auto park = [&](const Spinor<R>& p) {
-#pragma unroll
-        for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) stash[sp * 3 + c][threadIdx.x] = p.c[sp][c];
-    };
-    {
-        Spinor<R> own0;
-        load_spinor(own0, in, g.ldv, s3 + t0 * V3);
-        park(own0);
-    }
-    // the carried backward t-hop from slice t0 - 1 (also parked in LDS)
-    auto park_h = [&](const Z<R> (&h)[2][3]) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) hstash[q * 3 + c][threadIdx.x] = h[q][c];
-    };
-    {
-        Z<R> hb[2][3];
-        const int sp = s3 + ((t0 + g.nt - 1) % g.nt) * V3;
-        Z<R> u[3][3], h[2][3];
-        Spinor<R> p;
-        load_link(u, U, g.ldv, 3, sp);
-        load_spinor(p, in, g.ldv, sp);
-        if (g5_in) g5_inplace(p);
-        project<3, -1>(p, h);
-        adj_mat_vec(u, h, hb);
-        park_h(hb);
-    }
-#pragma unroll 1
-    for (int t = t0; t < t0 + T; ++t) {
-        const int s = s3 + t * V3;
-        Spinor<R> acc;
-#pragma unroll
-        for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) acc.c[sp][c] = mk<R>(0, 0);
-#pragma unroll 1
-        for (int nu = 0; nu < 3; ++nu) {
-            switch (nu) {
-                case 0: tm_hops_eager<0>(acc, U, in, g, s, n3.fwd[0] + t * V3, n3.bwd[0] + t * V3, g5_in); break;
-                case 1: tm_hops_eager<1>(acc, U, in, g, s, n3.fwd[1] + t * V3, n3.bwd[1] + t * V3, g5_in); break;
-                default: tm_hops_eager<2>(acc, U, in, g, s, n3.fwd[2] + t * V3, n3.bwd[2] + t * V3, g5_in); break;
-            }
-        }
-        // t: forward hop with psi(t+1), then the carried backward hop
-        Spinor<R> own;
-#pragma unroll
-        for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) own.c[sp][c] = stash[sp * 3 + c][threadIdx.x];
-        Z<R> ut[3][3];
-        Spinor<R> nxt;
-        load_link(ut, U, g.ldv, 3, s);
-        load_spinor(nxt, in, g.ldv, s3 + ((t + 1) % g.nt) * V3);
-        {
-            Spinor<R> p = nxt;
-            if (g5_in) g5_inplace(p);
-            hop_fwd<3>(acc, ut, p, ep);
-        }
-        {
-            Z<R> hb[2][3];
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-#pragma unroll
-                for (int c = 0; c < 3; ++c) hb[q][c] = hstash[q * 3 + c][threadIdx.x];
-            reconstruct_add<3, -1>(acc, hb, em);
-        }
-        // the next slice's backward t-hop: U_t(t)^dag P- psi(t)
-        {
-            Spinor<R> p = own;
-            if (g5_in) g5_inplace(p);
-            Z<R> h[2][3], hb[2][3];
-            project<3, -1>(p, h);
-            adj_mat_vec(ut, h, hb);
-            park_h(hb);
-        }
-        mem_fence_compiler();
-#pragma unroll
-        for (int sp = 0; sp < 4; ++sp) {
-            const R s_in = sp >= 2 ? s_in_hi : s_in_lo;
-            const R s_out = sp >= 2 ? s_out_hi : R(1);
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const Z<R> x = s_out * (s_in * own.c[sp][c] - kappa * acc.c[sp][c]);
-                R* q = reinterpret_cast<R*>(out + (size_t)(sp * 3 + c) * g.ldv + s);
-                __builtin_nontemporal_store(x.re, q);
-                __builtin_nontemporal_store(x.im, q + 1);
-            }
-        }
-        park(nxt);
-    }
-}
-
-// t-slices per chunk of the t-march: the largest divisor of nt that still gives
-// 512 workgroups, i.e. one wavefront on every SIMD (the kernel's 256 registers
-// allow one; measured at 32^4, 512 beat 256, 1024 and 2048); 0 when the tiles do
-// not split evenly over the XCDs.
+// t-slices per chunk of the marching operator without a timed pick: the largest divisor of
+// nt that still gives 512 groups of kBlock sites (1024 workgroups, two to four per compute
+// unit); 0 when the tiles do not split evenly over the XCDs.
 constexpr int kTmarchGroups = 512;
 inline int tmarch_chunk(const Geom& g) {
     const int V3 = g.nx * g.ny * g.nz;
@@ -683,25 +366,6 @@ int tmarch_chunks(const Geom& g, int* T, int maxn) {
     return n;
 }
 
-template <typename R, typename RL>
-void launch_apply(const Z<RL>* U, const Z<R>* in, Z<R>* out, const Geom& g, double kappa, double mu, int g5_in,
-                  int g5_out, hipStream_t st, Timing t, int tm_T) {
-    if (colour_grid(g.V)) {
-        timed_launch(k_apply<R, RL>, dim3(np_sten(g.V)), dim3(kSites), st, t, U, in, out, g, (R)kappa,
-                     (R)std::exp(mu), (R)std::exp(-mu), g5_in, g5_out);
-    } else if (const int T = tmarch_chunk(g) ? (tm_T > 0 && g.nt % tm_T == 0 ? tm_T : tmarch_chunk(g)) : 0) {
-        const int nb = g.nx * g.ny * g.nz / kBlock * (g.nt / T);
-        timed_launch(k_apply_tmarch<R, RL>, dim3(nb), dim3(kBlock), st, t, U, in, out, g, (R)kappa, (R)std::exp(mu),
-                     (R)std::exp(-mu), g5_in, g5_out, T);
-    } else {
-        const int nb = (grid_for(g.V) + kXcd - 1) / kXcd * kXcd;
-        const int slice = (g.nx * g.ny * g.nz) % (kBlock * kXcd) == 0;   // t-slices split evenly over XCDs
-        timed_launch(k_apply_site<R, RL>, dim3(nb), dim3(kBlock), st, t, U, in, out, g, (R)kappa, (R)std::exp(mu),
-                     (R)std::exp(-mu), g5_in, g5_out, slice);
-    }
-}
-
-// =============================================================== operator on canonical spinors
 // out = g5^{g5_out} (x - kappa hop x'), x' = g5^{g5_in} in, straight from the caller's
 // canonical array to the caller's canonical array.  A block of four wavefronts owns 64
 // consecutive sites, wavefront nu both hops of direction nu for every colour, so a site's
@@ -955,7 +619,7 @@ __global__ __launch_bounds__(kDirBlock) void k_apply_dirs(const Z<RL>* __restric
 
 // The march takes lattices whose (x, y, z) tiles split evenly over the XCDs.
 template <typename R, typename RL>
-void launch_apply_canonical(const Z<RL>* U, const ZD* in, ZD* out, const Geom& g, double kappa, double mu, int g5_in,
+void launch_apply(const Z<RL>* U, const ZD* in, ZD* out, const Geom& g, double kappa, double mu, int g5_in,
                             int g5_out, hipStream_t st, Timing t, int tm_T) {
     const R ep = (R)std::exp(mu), em = (R)std::exp(-mu);
     auto go = [&](auto kernel, int nb, int T) {
@@ -1454,6 +1118,290 @@ template <typename R>
 void launch_recur_replay(const Geom& g, const Work<R>& wk, const SrcList& L, Coef coef, int j, hipStream_t st) {
     dim3 grid((g.V + kPBlock - 1) / kPBlock, 12, L.n);
     hipLaunchKernelGGL(k_recur<R>, grid, dim3(kPBlock), 0, st, g, wk, L, coef, j, np_sten(g.V), 1);
+}
+
+// =============================================================== block-matrix process
+// Step j of the two-sided process on B = [[H, dH], [0, H]] (blocktsl.hip), halves as grid
+// dimension y: as the pair kernel of the plain process it normalises the residuals of step
+// j - 1 (v_j = r / beta_j into the basis, w_j = s / conj(gamma_j)), decides breakdown, forms
+// a = H v and b = H^dag w with shared link loads, adds the tangent (dH v_2 to the upper a,
+// dH^dag w_1 to the lower b) at the link's two sites and leaves partial sums of alpha_j and
+// |a|^2.  The coefficients are those of the 2n-vector: both halves' partial sums, upper
+// first.  Two launches a step in all, in place of four operator launches, a one-thread
+// tangent and three pointwise kernels: 15 us against 60 at 8^4.
+
+// The tangent term at site s, colour a, before normalisation: with dU = i X U_nu(s0),
+//   at s0: cf (1 + g_nu) dU in(s1),   at s1 = s0 + nu: cb (1 - g_nu) dU^dag in(s0).
+template <int NU>
+__device__ __forceinline__ void blk_tangent_dir(ZD (&acc)[4], const ZD* __restrict__ U, const BlockTangent& t,
+                                                const Geom& g, int a, int s, int s1, const ZD* __restrict__ in,
+                                                double cf, double cb) {
+    ZD u[3][3], row[3];
+    Spinor<double> p;
+    const bool here = s == t.site;
+    load_link(u, U, g.ldv, NU, t.site);
+    load_spinor(p, in, g.ldv, here ? s1 : t.site);
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        // dU[a][b] at s0, conj(dU[b][a]) at s1
+        ZD z = mk<double>(0, 0);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const int i = here ? a : b;
+            const ZD uc = here ? u[c][b] : (a == 0 ? u[c][0] : a == 1 ? u[c][1] : u[c][2]);
+            z = z + mk<double>(t.X[i][c][0], t.X[i][c][1]) * uc;
+        }
+        row[b] = here ? timesI(z) : cj(timesI(z));
+    }
+    if (here) hop1<NU, +1>(acc, row, p, cf);
+    else hop1<NU, -1>(acc, row, p, cb);
+}
+
+__device__ __forceinline__ void blk_tangent(ZD (&acc)[4], const ZD* __restrict__ U, const BlockTangent& t, const Geom& g,
+                                            int a, int s, int half, const BlockFields& f, int first, double emu) {
+    zero1(acc);
+    const Nbr n = neighbours(g, t.site);
+    const int s1 = t.nu == 0 ? n.fwd[0] : t.nu == 1 ? n.fwd[1] : t.nu == 2 ? n.fwd[2] : n.fwd[3];
+    if (s != t.site && s != s1) return;
+    // upper half: dH v_2; lower half: dH^dag w_1 (the factors of -mu)
+    const ZD* in = half == 0 ? (first ? f.x[1] : f.r[1]) : (first ? f.x[0] : f.s[0]);
+    const double e = half == 0 ? emu : 1.0 / emu;
+    switch (t.nu) {
+        case 0: blk_tangent_dir<0>(acc, U, t, g, a, s, s1, in, 1.0, 1.0); break;
+        case 1: blk_tangent_dir<1>(acc, U, t, g, a, s, s1, in, 1.0, 1.0); break;
+        case 2: blk_tangent_dir<2>(acc, U, t, g, a, s, s1, in, 1.0, 1.0); break;
+        default: blk_tangent_dir<3>(acc, U, t, g, a, s, s1, in, e, 1.0 / e); break;
+    }
+}
+
+// Block-uniform decisions and scalars of step j from the summed (omega, |r|^2, |s|^2) of
+// step j - 1: false when the process stops (recorded by one thread).
+__device__ __forceinline__ bool blk_scalars(const Coef& coef, int j, const double (&red)[kNvRecur], double& ib,
+                                            ZD& icg) {
+    const bool writer = blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0;
+    const ZD om = mk<double>(red[0], red[1]);
+    const double aom = sqrt(norm2(om));
+    if (j == 1) {
+        if (!(red[2] > 0.0 && std::isfinite(red[2]))) {   // zero source, or not finite
+            if (writer) {
+                coef.status[1] = 0;
+                coef.status[2] = red[2] > 0.0 ? 3 : 1;
+                coef.misc[0] = sqrt(red[2]);
+                *(volatile int*)coef.status = 1;
+            }
+            return false;
+        }
+    } else {
+        const bool lucky = red[2] <= kTauLucky * kTauLucky * coef.anorm2[j - 1];
+        const bool finite = std::isfinite(om.re) && std::isfinite(om.im);
+        const bool serious = !lucky && (!finite || aom <= kTauSerious * sqrt(red[2] * red[3]));
+        if (lucky || serious) {
+            if (writer) {
+                coef.status[1] = j - 1;
+                coef.status[2] = lucky ? 1 : 2;
+                coef.status[3] = j;
+                *(volatile int*)coef.status = 1;
+            }
+            return false;
+        }
+    }
+    const double beta = sqrt(aom);
+    const ZD gam = (1.0 / beta) * om;
+    if (writer) {
+        coef.beta[j] = beta;
+        coef.gamma[j] = gam;
+        if (j == 1) coef.misc[0] = beta;
+    }
+    ib = 1.0 / beta;
+    icg = zdiv(mk<double>(1.0, 0.0), cj(gam));
+    return true;
+}
+
+// v_j, w_j, a_j, b_j of colour a at site s (< V), and its share of the partial sums.
+__device__ __forceinline__ void blk_pair_site(const Geom& g, double kappa, const BlockFields& f, int half, int j, int a,
+                                              int s, double ib, ZD icg, const ZD (&acca)[4], const ZD (&accb)[4],
+                                              const ZD (&r0)[4], const ZD (&s0)[4], const ZD (&tan)[4],
+                                              double (&pv)[kNvBlk]) {
+    ZD v[4], w[4], av[4], bv[4];
+#pragma unroll
+    for (int sp = 0; sp < 4; ++sp) {
+        const double sg = sp < 2 ? 1.0 : -1.0;
+        const ZD d = (-kappa) * tan[sp];   // the tangent's share of the hop term (half 0: of a, half 1: of b)
+        v[sp] = ib * r0[sp];
+        w[sp] = icg * s0[sp];
+        av[sp] = (sg * ib) * (r0[sp] - kappa * acca[sp] + (half == 0 ? d : mk<double>(0, 0)));
+        bv[sp] = icg * (sg * (s0[sp] - kappa * accb[sp] + (half == 1 ? d : mk<double>(0, 0))));
+        const ZD wa = cjmul(w[sp], av[sp]);
+        pv[0] += wa.re;
+        pv[1] += wa.im;
+        pv[2] += norm2(av[sp]);
+    }
+    store1_nt(f.basis[half] + (size_t)(j - 1) * 12 * g.ldv, g.ldv, a, s, v);
+    store1_nt(f.w[half][j & 1], g.ldv, a, s, w);
+    store1_nt(f.a[half], g.ldv, a, s, av);
+    store1_nt(f.b[half], g.ldv, a, s, bv);
+}
+
+// Colour grid: wavefronts as in k_fwd_pair.
+__global__ __launch_bounds__(kRBlock) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void k_blk_pair_cg(const ZD* __restrict__ U, BlockTangent t, BlockFields f, Geom g, double kappa, double emu, Coef coef,
+                   int j, int npart_in) {
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kSites), l = threadIdx.x % kSites;
+    const int half = blockIdx.y, first = j == 1;
+    const ZD* rin = first ? f.x[half] : f.r[half];
+    const ZD* sin = first ? f.x[half] : f.s[half];
+    const int ncb = gridDim.x / 3;
+    const int a = blockIdx.x / ncb, s = (int)(blockIdx.x % ncb) * kSites + l;
+    __shared__ ZD xa[2][4][kSites], xb[2][4][kSites];
+    if (wv > 0) {
+        ZD acca[4], accb[4];
+        zero1(acca);
+        zero1(accb);
+        if (s < g.V) {
+            hop_half_pair(acca, accb, U, rin, sin, g, s, a, neighbours(g, s), emu, 1.0 / emu, wv - 1);
+            mem_fence_compiler();
+        }
+#pragma unroll
+        for (int sp = 0; sp < 4; ++sp) {
+            xa[wv - 1][sp][l] = acca[sp];
+            xb[wv - 1][sp][l] = accb[sp];
+        }
+        __syncthreads();
+        return;
+    }
+    double red[kNvRecur], lower[kNvRecur];
+    gather_partials<kNvRecur, kSites>(f.recur[0], npart_in, red);
+    gather_partials<kNvRecur, kSites>(f.recur[1], npart_in, lower);
+    const int stop = __builtin_amdgcn_readfirstlane(*(volatile const int*)coef.status);
+    ZD r0[4], s0[4], tan[4];
+    if (s < g.V) {
+        load1(r0, rin, g.ldv, a, s);
+        load1(s0, sin, g.ldv, a, s);
+        blk_tangent(tan, U, t, g, a, s, half, f, first, emu);
+    }
+#pragma unroll
+    for (int i = 0; i < kNvRecur; ++i) red[i] += lower[i];
+    wave_block_sum<kNvRecur>(red);
+    __syncthreads();
+    if (stop) return;
+    double ib;
+    ZD icg;
+    if (!blk_scalars(coef, j, red, ib, icg)) return;
+    double pv[kNvBlk] = {0.0, 0.0, 0.0};
+    if (s < g.V) {
+        ZD acca[4], accb[4];
+#pragma unroll
+        for (int sp = 0; sp < 4; ++sp) {
+            acca[sp] = xa[0][sp][l] + xa[1][sp][l];
+            accb[sp] = xb[0][sp][l] + xb[1][sp][l];
+        }
+        blk_pair_site(g, kappa, f, half, j, a, s, ib, icg, acca, accb, r0, s0, tan, pv);
+    }
+    wave_partials_at<kNvBlk>(f.pair[half], blockIdx.x, pv);
+}
+
+// Colour split: as k_fwd_pair_ms with one entry per workgroup.
+__global__ __launch_bounds__(kCBlock) void k_blk_pair_cs(const ZD* __restrict__ U, BlockTangent t, BlockFields f, Geom g,
+                                                         double kappa, double emu, Coef coef, int j, int npart_in) {
+    __shared__ HopX<double> x[1];
+    const int half = blockIdx.y, first = j == 1;
+    const ZD* rin[1] = {first ? f.x[half] : f.r[half]};
+    const ZD* sin[1] = {first ? f.x[half] : f.s[half]};
+    const int sb = sten_block<kCBlock>(g);
+    if (sb < 0) return;   // padding workgroup (uniform over the block)
+    __shared__ int stop;   // one read for the block: this launch may set the flag meanwhile
+    if (threadIdx.x == 0) stop = *(volatile const int*)coef.status;
+    __syncthreads();
+    if (stop) return;
+    double red[kNvRecur], lower[kNvRecur];
+    gather_partials<kNvRecur, kCBlock>(f.recur[0], npart_in, red);
+    gather_partials<kNvRecur, kCBlock>(f.recur[1], npart_in, lower);
+    const int a = wave_colour(), s = sb * kSites + threadIdx.x % kSites;
+    ZD acca[1][4], accb[1][4];
+    zero1(acca[0]);
+    zero1(accb[0]);
+    hop_all_pair_x<1>(acca, accb, U, rin, sin, 1u, g, s, a, emu, 1.0 / emu, x);
+    mem_fence_compiler();
+#pragma unroll
+    for (int i = 0; i < kNvRecur; ++i) red[i] += lower[i];
+    block_sum<kNvRecur, kCBlock>(red);
+    double ib;
+    ZD icg;
+    if (!blk_scalars(coef, j, red, ib, icg)) return;
+    double pv[kNvBlk] = {0.0, 0.0, 0.0};
+    if (s < g.V) {
+        ZD r0[4], s0[4], tan[4];
+        load1(r0, rin[0], g.ldv, a, s);
+        load1(s0, sin[0], g.ldv, a, s);
+        blk_tangent(tan, U, t, g, a, s, half, f, first, emu);
+        blk_pair_site(g, kappa, f, half, j, a, s, ib, icg, acca[0], accb[0], r0, s0, tan, pv);
+    }
+    write_partials_at<kNvBlk, kCBlock>(f.pair[half], sb, pv);
+}
+
+void launch_blk_pair(const ZD* U, const BlockTangent& t, const BlockFields& f, const Geom& g, double kappa, double mu,
+                     Coef coef, int j, hipStream_t st) {
+    const int npart_in = j == 1 ? grid_for(g.V) : np_point(g.V);
+    if (colour_grid(g.V))
+        hipLaunchKernelGGL(k_blk_pair_cg, dim3(np_colour(g.V), 2), dim3(kRBlock), 0, st, U, t, f, g, kappa,
+                           std::exp(mu), coef, j, npart_in);
+    else
+        hipLaunchKernelGGL(k_blk_pair_cs, dim3(g.nwg, 2), dim3(kCBlock), 0, st, U, t, f, g, kappa, std::exp(mu), coef,
+                           j, npart_in);
+}
+
+// Residuals of step j, one thread per (plane, site), halves as grid dimension z:
+// r = a - alpha v - gamma_j v_{j-1}, s = b - conj(alpha) w - beta_j w_{j-1}, with partial
+// sums of omega = s^H r, |r|^2, |s|^2; at j = k only alpha_j is recorded.
+__global__ __launch_bounds__(kPBlock) void k_blk_recur(BlockFields f, Geom g, Coef coef, int j, int k, int npart_in) {
+    const int half = blockIdx.z, s = blockIdx.x * kPBlock + threadIdx.x;
+    const size_t i = (size_t)blockIdx.y * g.ldv + s, fe = (size_t)12 * g.ldv;
+    const bool has_prev = j > 1, live = s < g.V && j < k;
+    ZD a_i = mk<double>(0, 0), b_i = a_i, v_i = a_i, w_i = a_i, vp_i = a_i, wp_i = a_i;
+    if (live) {
+        a_i = f.a[half][i];
+        b_i = f.b[half][i];
+        v_i = f.basis[half][(j - 1) * fe + i];
+        w_i = f.w[half][j & 1][i];
+        if (has_prev) {
+            vp_i = f.basis[half][(j - 2) * fe + i];
+            wp_i = f.w[half][(j - 1) & 1][i];
+        }
+    }
+    const ZD gj = has_prev ? coef.gamma[j] : mk<double>(0, 0);
+    const double bj = has_prev ? coef.beta[j] : 0.0;
+    double red[kNvBlk], lower[kNvBlk];
+    gather_partials<kNvBlk, kPBlock>(f.pair[0], npart_in, red);
+    gather_partials<kNvBlk, kPBlock>(f.pair[1], npart_in, lower);
+    mem_fence_compiler();
+    if (__builtin_amdgcn_readfirstlane(*(volatile const int*)coef.status)) return;   // written by the pair kernel only
+#pragma unroll
+    for (int q = 0; q < kNvBlk; ++q) red[q] += lower[q];
+    block_sum_last<kNvBlk, kPBlock>(red);
+    const ZD alpha = mk<double>(red[0], red[1]);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && half == 0 && threadIdx.x == 0) {
+        coef.alpha[j] = alpha;
+        coef.anorm2[j] = red[2];
+    }
+    if (j >= k) return;
+    double pv[kNvRecur] = {0.0, 0.0, 0.0, 0.0};
+    if (live) {
+        ZD r, q;
+        recur_update(a_i, b_i, v_i, w_i, vp_i, wp_i, alpha, cj(alpha), gj, bj, has_prev, r, q);
+        f.r[half][i] = r;
+        f.s[half][i] = q;
+        const ZD om = cjmul(q, r);
+        pv[0] = om.re;
+        pv[1] = om.im;
+        pv[2] = norm2(r);
+        pv[3] = norm2(q);
+    }
+    write_partials_at_last<kNvRecur, kPBlock>(f.recur[half], blockIdx.y * gridDim.x + blockIdx.x, pv);
+}
+
+void launch_blk_recur(const BlockFields& f, const Geom& g, Coef coef, int j, int k, hipStream_t st) {
+    const dim3 grid((g.V + kPBlock - 1) / kPBlock, 12, 2);
+    hipLaunchKernelGGL(k_blk_recur, grid, dim3(kPBlock), 0, st, f, g, coef, j, k, np_sten(g.V));
 }
 
 // out(s) = [psi(s) +] g5^{overlap} |x| sum_{j <= k_used} c_j v_j(s), canonical layout;
@@ -2297,9 +2245,7 @@ int launch_biorth(const Geom& g, const Work<R>& wk, const SrcList& L, Coef coef,
 
 // The stencil launchers for fields of type R and links of type RL.
 #define TSLOV_INST_STENCIL(R, RL)                                                                               \
-    template void launch_apply<R, RL>(const Z<RL>*, const Z<R>*, Z<R>*, const Geom&, double, double, int, int,  \
-                                      hipStream_t, Timing, int);                                                \
-    template void launch_apply_canonical<R, RL>(const Z<RL>*, const ZD*, ZD*, const Geom&, double, double, int, \
+    template void launch_apply<R, RL>(const Z<RL>*, const ZD*, ZD*, const Geom&, double, double, int, \
                                                 int, hipStream_t, Timing, int);                                 \
     template void launch_fwd_pair<R, RL>(const Z<RL>*, const Geom&, double, double, const Work<R>&,             \
                                          const SrcList&, Coef, int, int, int, hipStream_t, Timing);             \

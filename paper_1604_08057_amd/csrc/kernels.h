@@ -24,17 +24,14 @@ template <typename R>
 void launch_spinor_from_soa(const Z<R>* in, ZD* out, const Geom& g, hipStream_t st);
 
 // ---------------------------------------------------------------- operator
-// out = G5out * (G5in in - kappa * hop_{mu}(G5in in))
+// out = G5out * (G5in in - kappa * hop_{mu}(G5in in)) on canonical spinors (float64 complex,
+// caller's arrays), fields rounded to R.  tm_T: the t-slices per chunk of a marching
+// lattice (0: the built-in choice; every choice gives the same result).
 template <typename R, typename RL>
-void launch_apply(const Z<RL>* U, const Z<R>* in, Z<R>* out, const Geom& g, double kappa, double mu,
-                  int g5_in, int g5_out, hipStream_t st, Timing t = {}, int tm_T = 0);
-// The same on canonical spinors (float64 complex, caller's arrays), fields rounded to R.
-template <typename R, typename RL>
-void launch_apply_canonical(const Z<RL>* U, const ZD* in, ZD* out, const Geom& g, double kappa, double mu, int g5_in,
+void launch_apply(const Z<RL>* U, const ZD* in, ZD* out, const Geom& g, double kappa, double mu, int g5_in,
                             int g5_out, hipStream_t st, Timing t = {}, int tm_T = 0);
-// The t-slices per chunk the t-march operator can run this lattice with (each
-// gives the same result), at most maxn of them into T; 0 when it does not apply.
-// launch_apply's tm_T picks one (0: the built-in choice).
+// The t-slices per chunk the marching operator can run this lattice with, at most maxn
+// of them into T; 0 when it does not apply.
 int tmarch_chunks(const Geom& g, int* T, int maxn);
 
 // ---------------------------------------------------------------- batch workspace
@@ -284,28 +281,29 @@ struct BlockTangent {
     int nu, site;
     double X[3][3][2];
 };
-// Float64 SoA fields of the block process, [0] upper and [1] lower half: the source
-// x, the current and previous vectors, the products (then the residuals), and the
-// basis (step j at basis[h] + (j - 1) 12 ldv).
+// Float64 SoA fields of the block process, [0] upper and [1] lower half: the source x, the
+// residuals r, s, the products a, b, the left vectors w_j at [j & 1], the right basis
+// (v_j at basis[h] + (j - 1) 12 ldv) and the partial sums of the pair and recurrence kernels.
 struct BlockFields {
     ZD* x[2];
-    ZD* v[2];
-    ZD* w[2];
-    ZD* vp[2];
-    ZD* wp[2];
+    ZD* r[2];
+    ZD* s[2];
     ZD* a[2];
     ZD* b[2];
+    ZD* w[2][2];
     ZD* basis[2];
+    double* pair[2];    // alpha re/im, |a|^2 (kNvBlk per block)
+    double* recur[2];   // omega re/im, |r|^2, |s|^2 (kNvRecur); |x|^2 before the first step
 };
-int blk_blocks(const Geom& g);   // partial-sum blocks of the block-process kernels
+constexpr int kNvBlk = 3;
 // out_a += dH in_a, out_b += dH^dag in_b (either pair null) for the tangent t.
 void launch_blk_tangent(const ZD* U, const BlockTangent& t, const Geom& g, double kappa, double mu, const ZD* in_a,
                         ZD* out_a, const ZD* in_b, ZD* out_b, hipStream_t st);
-// v_1 = w_1 = x / |x| (|x| in coef.misc[0]; a zero source stops with k_used = 0).
-void launch_blk_start(const BlockFields& f, const Geom& g, Coef coef, double* part, hipStream_t st);
-// The recursion of step j after the products a = B v_j, b = B^H w_j (p0, p1: partials).
-void launch_blk_step(const BlockFields& f, const Geom& g, Coef coef, double* p0, double* p1, int j, int k,
-                     hipStream_t st);
+// Step j of k of the block process: the pair kernel, then the recurrence (residuals of
+// step j, at j = k alpha_k only).
+void launch_blk_pair(const ZD* U, const BlockTangent& t, const BlockFields& f, const Geom& g, double kappa, double mu,
+                     Coef coef, int j, hipStream_t st);
+void launch_blk_recur(const BlockFields& f, const Geom& g, Coef coef, int j, int k, hipStream_t st);
 
 // ---------------------------------------------------------------- nested step
 // Inner two-sided Lanczos process of the nested projected-matrix step (nested.hip)
