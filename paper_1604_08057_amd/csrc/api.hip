@@ -136,6 +136,7 @@ struct tslov_ctx {
     double kappa = 0.0, mu = 0.0;
     int antiperiodic = 1, precision = TSLOV_FP64;
     hipStream_t st = nullptr;
+    hipStream_t side = nullptr;   // the sign calls' Ritz values, beside the projected-matrix step
     int device = 0;
     size_t lds_max = 65536;
     int links_set = 0;
@@ -155,6 +156,7 @@ struct tslov_ctx {
     Buf fields, part, coefmem;
     Buf dense, denseInt, densePart, denseDelta;
     Buf rat;         // rational sign step: pole plane, row partials, estimate
+    Buf ritz;        // device Ritz summary (three doubles)
     Buf gpart, gsrc;
     Buf bout;        // per-entry canonical y and dpsi (Ward check)
     Buf wardp;       // Ward block maxima
@@ -596,6 +598,42 @@ struct RitzJobs {
         th.clear();
     }
     ~RitzJobs() { join(); }
+};
+
+// Largest k whose Ritz summary a sign call forms on the device (one compute unit: 1.0 ms at
+// k = 200 and 2.6 ms at k = 400, against 1.1 and 3.8 ms on host threads; the work grows with
+// k^2, and beyond this one compute unit is no faster than four threads).
+constexpr int kRitzDeviceMax = 512;
+
+// The Ritz summary of a sign call on the device: on a stream of its own, started when the
+// forward pass has ended (the host has waited for it) and joined before the call returns,
+// on every path.  The coefficients it reads are not written in between.
+struct RitzOnDevice {
+    tslov_ctx* c;
+    bool busy = false;
+    explicit RitzOnDevice(tslov_ctx* ctx) : c(ctx) {}
+    RitzOnDevice(const RitzOnDevice&) = delete;
+    RitzOnDevice& operator=(const RitzOnDevice&) = delete;
+    ~RitzOnDevice() {
+        if (busy) (void)hipStreamSynchronize(c->side);
+    }
+    tslov_status start(int k) {
+        if (!c->side) HIPCHK(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
+        CHK(ensure(c->ritz, 3 * sizeof(double)));
+        tslov::launch_ritz(c->coef.at(0), k, c->ritz.as<double>(), c->side);
+        HIPCHK(hipGetLastError());
+        busy = true;
+        return TSLOV_OK;
+    }
+    tslov_status join(tslov::RitzSummary& r) {
+        if (!busy) return TSLOV_OK;
+        double h[3];
+        HIPCHK(hipMemcpyAsync(h, c->ritz.p, sizeof(h), hipMemcpyDeviceToHost, c->side));
+        HIPCHK(hipStreamSynchronize(c->side));
+        busy = false;
+        r = tslov::RitzSummary{h[0], h[1], (int)h[2]};
+        return TSLOV_OK;
+    }
 };
 
 // A Ritz value on the imaginary axis (relative to the size of T_k) leaves the sign
@@ -1277,12 +1315,15 @@ tslov_status sign_impl(tslov_ctx* c, const void* psi_in, void* out, int k, const
     CHK(ensure_work(c, 1, k, 0));
     const SrcList L = make_list({0}, {k});
     std::vector<EntryStatus> es;
+    const bool ritz_here = k <= kRitzDeviceMax;
     RitzJobs jobs;
-    CHK((forward<R, RL>(c, L, src, nullptr, 0, es, &jobs)));
+    CHK((forward<R, RL>(c, L, src, nullptr, 0, es, ritz_here ? nullptr : &jobs)));
     if (es[0].breakdown == 2)
         return fail(TSLOV_ERR_BREAKDOWN, "serious Lanczos breakdown at step " + std::to_string(es[0].step));
     const double t1 = now_ms();
     const int k_used = es[0].k_used;
+    RitzOnDevice ritz(c);
+    if (ritz_here && k_used > 0) CHK(ritz.start(k_used));
     SrcList Ld = make_list({0}, {k_used});
     std::vector<int> stag(1, 0);
     if (k_used > 0) {
@@ -1313,8 +1354,11 @@ tslov_status sign_impl(tslov_ctx* c, const void* psi_in, void* out, int k, const
     }
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(c->st));
-    jobs.join();
-    es[0].ritz = jobs.out[0];
+    CHK(ritz.join(es[0].ritz));
+    if (!ritz_here) {
+        jobs.join();
+        es[0].ritz = jobs.out[0];
+    }
     es[0].flags = entry_flags(c, es[0], stag[0], 0);
     CHK(check_ritz(es[0]));
     const double t3 = now_ms();
@@ -2068,12 +2112,13 @@ void tslov_destroy(tslov_ctx* c) {
     if (!c) return;
     (void)hipStreamSynchronize(c->st);
     for (Buf* b : {&c->trial, &c->solvebuf, &c->physbuf, &c->U64, &c->U32, &c->badflag, &c->nestbuf, &c->blk, &c->bdefl, &c->deflb, &c->curdefl, &c->sbmap, &c->basisV, &c->basisW, &c->basisA, &c->basisB, &c->abarS, &c->sbarS,
-                   &c->fields, &c->part, &c->coefmem, &c->dense, &c->rat, &c->denseInt, &c->densePart, &c->denseDelta,
+                   &c->fields, &c->part, &c->coefmem, &c->dense, &c->rat, &c->ritz, &c->denseInt, &c->densePart, &c->denseDelta,
                    &c->gpart, &c->gsrc, &c->bout, &c->wardp, &c->canon, &c->deflw, &c->deflx, &c->cgf, &c->cgp,
                    &c->cgs, &c->ckpt})
         release(*b);
     c->gfwd.reset();
     c->gbwd.reset();
+    if (c->side) (void)hipStreamDestroy(c->side);
     if (c->host_part) (void)hipHostFree(c->host_part);
     for (auto& v : c->ev_used)
         for (auto& pr : v) {
