@@ -497,14 +497,13 @@ tslov_status tslov_get_pair_ns(const tslov_ctx* ctx, int* fwd_ns, int* bwd_ns);
  *   form = 1: colour split, two systems per workgroup;
  *   form = 2: the multi-right-hand-side layout with the link times half-spinor
  *            products on the float64 matrix cores (v_mfma_f64_16x16x4f64);
- *   form = 3 (the default): each thread marches one (x, y, z) site of one system
- *            along t, the systems of a tile running back to back on one XCD.
+ *   form = 3 (the default): a wavefront per direction, the links of 64 sites kept
+ *            in registers over the systems of a workgroup.
  * The results agree to rounding (the forms differ in the summation order of the
- * residual norms and, on the matrix cores, of the link products).  Form 3 needs an
- * (x, y, z) volume in multiples of 1024 sites and runs form 0 otherwise; forms 0
- * and 2 need 7 * 5 * 12 * ldv + ldv complex doubles to stay below 4 GiB (lattices
- * up to about 639,000 sites) and run form 1 above that.  ERR_ARG for any other
- * form. */
+ * residual norms and, on the matrix cores, of the link products).  Form 3 runs on
+ * every lattice; forms 0 and 2 need 7 * 5 * 12 * ldv + ldv complex doubles to stay
+ * below 4 GiB (lattices up to about 639,000 sites) and run form 1 above that.
+ * ERR_ARG for any other form. */
 tslov_status tslov_set_cg_operator(tslov_ctx* ctx, int form);
 
 /* Algorithmic bytes moved by one launch of kernel class `which` (see above) for

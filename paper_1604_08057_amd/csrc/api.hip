@@ -193,7 +193,7 @@ struct tslov_ctx {
     // -1: the operator does not march on this lattice) and a forced value
     int tm_T = 0, tm_T_forced = 0;
     // operator form of the shifted solves of the deflated derivative (tslov::kCgOp*)
-    int cg_op = tslov::kCgOpTmarch;
+    int cg_op = tslov::kCgOpLinks;
 
     int nblk() const { return tslov::grid_for(g.V); }
     size_t field_elems() const { return (size_t)12 * g.ldv; }
@@ -1554,6 +1554,7 @@ tslov_status cg_solve(tslov_ctx* c, int nr, const tslov::CgWork& cw, int* iters)
             for (int e = 0; e < nr; ++e) all_done &= sh[e].done;
         }
     }
+    tslov::launch_cg_end(c->g, nr, cw, c->st);
     *iters = it;
     if (!all_done) return fail(TSLOV_ERR_NOT_CONVERGED, "shifted solves of the eigenpair derivative did not converge");
     return TSLOV_OK;
@@ -2728,7 +2729,7 @@ tslov_status tslov_set_pair_ns(tslov_ctx* c, int ns) {
 
 tslov_status tslov_set_cg_operator(tslov_ctx* c, int form) {
     if (!c) return fail(TSLOV_ERR_ARG, "null context");
-    if (form < tslov::kCgOpMulti || form > tslov::kCgOpTmarch) return fail(TSLOV_ERR_ARG, "form must be 0, 1, 2 or 3");
+    if (form < tslov::kCgOpMulti || form > tslov::kCgOpLinks) return fail(TSLOV_ERR_ARG, "form must be 0, 1, 2 or 3");
     c->cg_op = form;
     return TSLOV_OK;
 }

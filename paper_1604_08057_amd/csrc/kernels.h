@@ -182,14 +182,15 @@ struct CgRhs {
     double bnorm2;   // |b|^2
     double zeta[2];  // |A^dag r|^2, double-buffered by iteration parity
     double rr;       // |r|^2 at the last check
+    double alpha;    // step length of the last iteration
     int done;        // converged (frozen)
     int pad;
 };
 constexpr int kCgX = 0, kCgR = 1, kCgP = 2, kCgW = 3, kCgZ = 4, kCgFields = 5;
-// Operator forms of the shifted solves (all give the same hop sums; the partial sums
-// of |A p|^2 differ in their summation order): multi-right-hand-side site per thread
-// (default), colour split with two systems per block.
-constexpr int kCgOpMulti = 0, kCgOpColour = 1, kCgOpMfma = 2, kCgOpTmarch = 3;
+// Operator forms of the shifted solves (all give the same hop sums; the summation order of
+// the residual norms differs): multi-right-hand-side site per thread, colour split with two
+// systems per block, matrix cores, and the default, whose blocks keep their links.
+constexpr int kCgOpMulti = 0, kCgOpColour = 1, kCgOpMfma = 2, kCgOpLinks = 3;
 struct CgWork {
     ZD* f;        // [e][kCgFields] float64 SoA fields
     double* part; // [e][4][pstride]
@@ -212,6 +213,8 @@ void launch_cg_start(const ZD* U, const Geom& g, double kappa, double mu, int nr
 // one CGNR iteration (check = 1: evaluate convergence afterwards)
 void launch_cg_iteration(const ZD* U, const Geom& g, double kappa, double mu, int nr, int it, int check, double tol,
                          const CgWork& cw, hipStream_t st);
+// what the last iterations left to add to the solutions
+void launch_cg_end(const Geom& g, int nr, const CgWork& cw, hipStream_t st);
 // projections (1 - Pi_i) / (1 - Pi_i^H) of the solutions and the conj(c_i) scaling
 void launch_cg_finish(const Geom& g, const ZD* R, const ZD* L, const ZD* c, int l, const CgWork& cw, hipStream_t st);
 // U(1) projections -Im tr(G_e^H U) of nsrc canonical link gradients dU[e] into gsrc[e][4][ldv]

@@ -15,6 +15,7 @@
 // canonical [V][4][3] arrays of the caller.
 #include "kernels.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace tslov {
@@ -165,23 +166,6 @@ __device__ __forceinline__ void mr_hops(Spinor<double>& acc, const ZD* __restric
     hop_bwd<NU>(acc, u, p, NU == 3 ? em : 1.0);
 }
 
-// Both hops of direction NU for a whole site of the t-march form, the four operands'
-// loads issued before any arithmetic (one memory round trip per direction).
-template <int NU>
-__device__ __forceinline__ void tm_cg_hops(Spinor<double>& acc, const ZD* __restrict__ U, const ZD* __restrict__ in,
-                                           const Geom& g, int s, int sf, int sb) {
-    ZD uf[3][3], ub[3][3];
-    Spinor<double> pf, pb;
-    load_link(uf, U, g.ldv, NU, s);
-    load_spinor(pf, in, g.ldv, sf);
-    load_link(ub, U, g.ldv, NU, sb);
-    load_spinor(pb, in, g.ldv, sb);
-    cg_fence_compiler();
-    hop_fwd<NU>(acc, uf, pf, 1.0);
-    hop_bwd<NU>(acc, ub, pb, 1.0);
-}
-
-
 }  // namespace
 
 // Multi-right-hand-side form of out_e = A_e in_e (A_e as for k_cg_apply): one
@@ -251,121 +235,158 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 2))) v
     if (live && lane % 8 == 0) cw.p(e, preg)[sb] = pv;
 }
 
-// ---------------------------------------------------------------- t-march form
-// The operator with a march along t (the t-march of the plain operator, per system): a
-// block of kBlock threads owns a tile of kBlock (x, y, z) sites of one system and runs
-// through a chunk of T consecutive t-slices.  psi(t+1), loaded for the forward t-hop of
-// slice t, is the own spinor of slice t+1, and the backward t-hop of slice t+1 before
-// reconstruction, U_t(t)^dag P- psi(t), is carried: along t every spinor and link is
-// read once per chunk.  Both wait in LDS slots private to the thread while the x, y, z
-// hops hold the registers.  The blocks of one (tile, chunk) for all systems run
-// back to back on one XCD (block b: XCD b % 8; system (b / 8) % nr; then tile and chunk,
-// each XCD taking the same run of tiles, a slab of z-planes, in every chunk), so the
-// systems read the tile's links from that XCD's L2.  Each x, y, z direction issues its
-// four operands before any arithmetic (one round trip; loading the backward hop's after
-// the forward hop's arithmetic took 7.62 instead of 7.50 s per 16^4 derivative).  Hop
-// sum in the order of the other forms (x, y, z, t; forward then backward).  Partials of
-// |out_e|^2 per (tile, chunk).
-__global__ __launch_bounds__(kBlock) void k_cg_apply_tm(const ZD* __restrict__ U, Geom g, double kappa, double emu,
-                                                        CgWork cw, int nr, int adj, int in_field, int out_field,
-                                                        int preg, int T) {
-    const int V3 = g.nx * g.ny * g.nz, per = V3 / kBlock / kXcd;
-    const int m = blockIdx.x / kXcd, e = m % nr, rest = m / nr;
-    const int tile = (blockIdx.x % kXcd) * per + rest % per, chunk = rest / per;
-    if (*(volatile const int*)&cw.st[e].done) return;   // uniform over the block
-    const CgRhs* st = cw.st + e;
-    const ZD sig = adj ? cj(st->sigma) : st->sigma;
-    const double msg = adj ? -st->msign : st->msign;
-    const double ep = msg > 0 ? emu : 1.0 / emu, em = 1.0 / ep;
-    const ZD* __restrict__ in = cw.field(e, in_field);
-    ZD* __restrict__ out = cw.field(e, out_field);
-    const int s3 = tile * kBlock + threadIdx.x;   // the (x, y, z) site; t = 0
-    const int t0 = chunk * T;
-    const Nbr n3 = neighbours(g, s3);
-    __shared__ ZD stash[12][kBlock];
-    __shared__ ZD hstash[6][kBlock];
-    auto park = [&](const Spinor<double>& p) {
+// ---------------------------------------------------------------- link-resident form
+// out_e = A_e in_e (A_e as for k_cg_apply) with a wavefront per direction: a block of four
+// wavefronts owns 64 consecutive sites, keeps their eight links in registers and goes
+// through a chunk of the systems.  Wavefront nu loads a system's two neighbour spinors of
+// direction nu (while the system before is summed) and leaves the link-applied half spinors
+// in LDS; after the barrier it adds the eight hops of spin component nu in the order of the
+// other forms (x, y, z, t; forward, backward) and forms the result.  Partials of |out_e|^2
+// per site block, the spin components' sums in order.
+// Bound by the fields' way from the memory-side cache: a system's field is read once and
+// again at the edges of each die's run of sites (2 x for runs of two z-planes), written once.
+// 16^3 x 4, 16 systems: 30.3 us (5.3 TB/s with that), against 37.7 us marching t per site
+// and 39.1 us with this layout but the links loaded per system.  Forming the vector updates
+// inside the operator launches (p' = z + beta p and r' = r - alpha w at every neighbour; two
+// launches per iteration) took 85 and 62 us: the edges' rereads double.
+constexpr int kCgBlock = 4 * kSites;
+constexpr int kCgChunk = 64;        // systems per block at most (flags in LDS)
+constexpr int kCgFill = 512;        // blocks that fill the chip: two per CU
+
+// One spin component of recon1_add: acc += coef * [h; L h]_SP for the half spinors t.
+template <int NU, int S, int SP>
+__device__ __forceinline__ void cg_add_spin(ZD& acc, const ZD (*t)[kSites], int c, int l, double coef) {
+    constexpr int from = SP < 2 ? SP : (NU < 2 ? 3 - SP : SP - 2);   // the half spinor that SP is built from
+    ZD full[4], o[2];
+    full[SP] = acc;
+    o[from] = t[from * 3 + c][l];
+    o[1 - from] = mk<double>(0, 0);
 #pragma unroll
-        for (int sp = 0; sp < 4; ++sp)
+    for (int i = 0; i < 4; ++i)
+        if (i != SP) full[i] = mk<double>(0, 0);
+    recon1_add<NU, S>(full, o, coef);
+    acc = full[SP];
+}
+
+struct CgShared {
+    ZD hops[4][12][kSites];
+    double sum[kCgChunk][4];
+    int live[kCgChunk + 1];   // the chunk's live systems, ascending; -1 behind the last
+};
+
+// The work of wavefront W: hops of direction W, then spin component W of the sum.
+template <int W>
+__device__ __forceinline__ void cg_wave(CgShared& sh, const ZD* __restrict__ U, const Geom& g, double kappa,
+                                        double emu, const CgWork& cw, int adj, int in_field, int out_field, int s) {
+    const int l = threadIdx.x % kSites;
+    const int sc = min(s, g.V - 1);
+    const Nbr n = neighbours(g, sc);
+    ZD uf[3][3], ub[3][3];
+    Spinor<double> pf, pb;
+    int e = __builtin_amdgcn_readfirstlane(sh.live[0]);
+    load_spinor(pf, cw.field(e, in_field), g.ldv, n.fwd[W]);
+    load_link(uf, U, g.ldv, W, sc);
+    load_link(ub, U, g.ldv, W, n.bwd[W]);
+    for (int i = 0; e >= 0; ++i) {
+        const int next = __builtin_amdgcn_readfirstlane(sh.live[i + 1]);
+        const FieldBase fi = field_base(cw.field(e, in_field)), fo = field_base(cw.field(e, out_field));
+        const CgRhs* st = cw.st + e;
+        ZD x[3];
+        {
+            ZD h[2][3], o[2][3];
+            project<W, +1>(pf, h);
+            cg_fence_compiler();
+            load_spinor(pb, cw.field(e, in_field), g.ldv, n.bwd[W]);
 #pragma unroll
-            for (int c = 0; c < 3; ++c) stash[sp * 3 + c][threadIdx.x] = p.c[sp][c];
-    };
-    auto park_h = [&](const ZD (&h)[2][3]) {
+            for (int c = 0; c < 3; ++c) x[c] = fload<double>(fi, g.ldv, W * 3 + c, (unsigned)sc);
+            cg_fence_compiler();
+            mat_vec(uf, h, o);
 #pragma unroll
-        for (int q = 0; q < 2; ++q)
+            for (int sp = 0; sp < 2; ++sp)
 #pragma unroll
-            for (int c = 0; c < 3; ++c) hstash[q * 3 + c][threadIdx.x] = h[q][c];
-    };
-    {
-        Spinor<double> own0;
-        load_spinor(own0, in, g.ldv, s3 + t0 * V3);
-        park(own0);
-    }
-    {
-        const int sp = s3 + ((t0 + g.nt - 1) % g.nt) * V3;
-        ZD u[3][3], h[2][3], hb[2][3];
-        Spinor<double> p;
-        load_link(u, U, g.ldv, 3, sp);
-        load_spinor(p, in, g.ldv, sp);
-        project<3, -1>(p, h);
-        adj_mat_vec(u, h, hb);
-        park_h(hb);
-    }
-    double pv = 0.0;
-#pragma unroll 1
-    for (int t = t0; t < t0 + T; ++t) {
-        const int s = s3 + t * V3;
-        Spinor<double> acc;
-        zero_spinor(acc);
-#pragma unroll 1
-        for (int nu = 0; nu < 3; ++nu) {
-            switch (nu) {
-                case 0: tm_cg_hops<0>(acc, U, in, g, s, n3.fwd[0] + t * V3, n3.bwd[0] + t * V3); break;
-                case 1: tm_cg_hops<1>(acc, U, in, g, s, n3.fwd[1] + t * V3, n3.bwd[1] + t * V3); break;
-                default: tm_cg_hops<2>(acc, U, in, g, s, n3.fwd[2] + t * V3, n3.bwd[2] + t * V3); break;
+                for (int c = 0; c < 3; ++c) sh.hops[W][sp * 3 + c][l] = o[sp][c];
+            project<W, -1>(pb, h);
+            cg_fence_compiler();
+            if (next >= 0) load_spinor(pf, cw.field(next, in_field), g.ldv, n.fwd[W]);
+            cg_fence_compiler();
+            adj_mat_vec(ub, h, o);
+#pragma unroll
+            for (int sp = 0; sp < 2; ++sp)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) sh.hops[W][6 + sp * 3 + c][l] = o[sp][c];
+        }
+        __syncthreads();
+        const ZD sig = adj ? cj(st->sigma) : st->sigma;
+        const double msg = adj ? -st->msign : st->msign;
+        const double ep = msg > 0 ? emu : 1.0 / emu, em = 1.0 / ep;
+        double po = 0.0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            ZD acc = mk<double>(0, 0);
+            cg_add_spin<0, +1, W>(acc, sh.hops[0], c, l, 1.0);
+            cg_add_spin<0, -1, W>(acc, sh.hops[0] + 6, c, l, 1.0);
+            cg_add_spin<1, +1, W>(acc, sh.hops[1], c, l, 1.0);
+            cg_add_spin<1, -1, W>(acc, sh.hops[1] + 6, c, l, 1.0);
+            cg_add_spin<2, +1, W>(acc, sh.hops[2], c, l, 1.0);
+            cg_add_spin<2, -1, W>(acc, sh.hops[2] + 6, c, l, 1.0);
+            cg_add_spin<3, +1, W>(acc, sh.hops[3], c, l, ep);
+            cg_add_spin<3, -1, W>(acc, sh.hops[3] + 6, c, l, em);
+            const double g5 = W < 2 ? 1.0 : -1.0;
+            const ZD out = sig * x[c] - g5 * (x[c] - kappa * acc);
+            if (s < g.V) {
+                fstore<double>(fo, g.ldv, W * 3 + c, (unsigned)s, out);
+                po += norm2(out);
             }
         }
-        Spinor<double> own;
-#pragma unroll
-        for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) own.c[sp][c] = stash[sp * 3 + c][threadIdx.x];
-        ZD ut[3][3];
-        Spinor<double> nxt;
-        load_link(ut, U, g.ldv, 3, s);
-        load_spinor(nxt, in, g.ldv, s3 + ((t + 1) % g.nt) * V3);
-        hop_fwd<3>(acc, ut, nxt, ep);
-        {
-            ZD hb[2][3];
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-#pragma unroll
-                for (int c = 0; c < 3; ++c) hb[q][c] = hstash[q * 3 + c][threadIdx.x];
-            reconstruct_add<3, -1>(acc, hb, em);
-        }
-        {
-            ZD h[2][3], hb[2][3];
-            project<3, -1>(own, h);
-            adj_mat_vec(ut, h, hb);
-            park_h(hb);
-        }
-        cg_fence_compiler();
-#pragma unroll
-        for (int sp = 0; sp < 4; ++sp) {
-            const double g5 = sp < 2 ? 1.0 : -1.0;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const ZD x = own.c[sp][c];
-                const ZD o = sig * x - g5 * (x - kappa * acc.c[sp][c]);
-                out[(size_t)(sp * 3 + c) * g.ldv + s] = o;
-                pv += norm2(o);
-            }
-        }
-        park(nxt);
+        po = wave_sum(po);
+        if (l == 0) sh.sum[i][W] = po;
+        __syncthreads();   // the half spinors are read before the next system's come
+        e = next;
     }
-    double red[1] = {pv};
-    block_sum_last<1, kBlock>(red);
-    if (threadIdx.x == 0) cw.p(e, preg)[tile * (g.nt / T) + chunk] = red[0];
+}
+
+// Site block of unit u of an XCD's share of `per` units (-1: padding): the same run of
+// every t-slice where the slices split evenly, else a contiguous run.
+__device__ __forceinline__ int cg_unit_block(const Geom& g, int xcd, int u, int per) {
+    const int n3 = g.nx * g.ny * g.nz / kSites;
+    if (g.nx * g.ny * g.nz % (kSites * kXcd) == 0) {
+        const int p3 = n3 / kXcd;
+        return (u / p3) * n3 + xcd * p3 + u % p3;
+    }
+    const int sb = xcd * per + u;
+    return sb < np_stencil(g.V) ? sb : -1;
+}
+
+__global__ __launch_bounds__(kCgBlock, 2) void k_cg_apply_links(const ZD* __restrict__ U, Geom g, double kappa,
+                                                                double emu, CgWork cw, int nr, int adj, int in_field,
+                                                                int out_field, int preg, int per, int ns) {
+    __shared__ CgShared sh;
+    const int m = blockIdx.x / kXcd;
+    const int sb = cg_unit_block(g, blockIdx.x % kXcd, m % per, per);
+    if (sb < 0) return;   // uniform over the block, as the next
+    const int e0 = m / per * ns;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kSites), l = threadIdx.x % kSites;
+    // the chunk's live systems, found by every wavefront, written by the first
+    const bool live = l < min(ns, nr - e0) && !*(volatile const int*)&cw.st[e0 + l].done;
+    const unsigned long long mask = __ballot(live);
+    const int nlive = __popcll(mask);
+    if (!nlive) return;
+    if (w == 0) {
+        if (live) sh.live[__popcll(mask & ((1ull << l) - 1))] = e0 + l;
+        if (l == 0) sh.live[nlive] = -1;
+    }
+    __syncthreads();
+    const int s = sb * kSites + l;
+    switch (w) {
+        case 0: cg_wave<0>(sh, U, g, kappa, emu, cw, adj, in_field, out_field, s); break;
+        case 1: cg_wave<1>(sh, U, g, kappa, emu, cw, adj, in_field, out_field, s); break;
+        case 2: cg_wave<2>(sh, U, g, kappa, emu, cw, adj, in_field, out_field, s); break;
+        default: cg_wave<3>(sh, U, g, kappa, emu, cw, adj, in_field, out_field, s); break;
+    }
+    for (int i = threadIdx.x; i < nlive; i += kCgBlock) {
+        const double* po = sh.sum[i];
+        cw.p(sh.live[i], preg)[sb] = ((po[0] + po[1]) + po[2]) + po[3];
+    }
 }
 
 // ---------------------------------------------------------------- matrix-core form
@@ -521,41 +542,23 @@ __global__ __launch_bounds__(kWave) void k_cg_apply_mfma(const ZD* __restrict__ 
 
 namespace {
 
-// t-slices per chunk of the t-march form: the whole time extent when the tiles and systems
-// give at least 512 workgroups, else the largest divisor of nt that does; 0 when the
-// (x, y, z) volume does not split into tiles of kBlock sites evenly over the XCDs.
-int cg_tm_chunk(const Geom& g, int nr) {
-    const int V3 = g.nx * g.ny * g.nz;
-    if (V3 % (kBlock * kXcd) != 0) return 0;
-    const long long nb = (long long)V3 / kBlock * nr;
-    int T = 1;
-    for (int c = 1; c <= g.nt; ++c)
-        if (g.nt % c == 0 && nb * (g.nt / c) >= 512) T = c;
-    return T;
-}
-
-// Partial sums per system written by one operator launch.
-int cg_apply_parts(const Geom& g, int nr, int op) {
-    if (op == kCgOpTmarch && cg_tm_chunk(g, nr) > 0) return g.nx * g.ny * g.nz / kBlock * (g.nt / cg_tm_chunk(g, nr));
-    return np_stencil(g.V);
-}
-
-// The operator launch over the nr systems.  Forms (measured at 16^4 with 40 systems, per
-// deflated derivative): t-march 7.50 s, multi-right-hand-side 7.70 s, colour split
-// 7.82 s, matrix-core 14.2 s.  The t-march form needs (x, y, z) volumes in multiples of
-// 1024 sites and otherwise runs the multi-right-hand-side form; the eight-system forms
-// address a wavefront's systems with 32-bit offsets from the first one's planes and
+// The operator launch over the nr systems.  The link-resident form serves every lattice and
+// number of systems; the others stay selectable (16^4, 40 systems, per deflated derivative:
+// multi-right-hand-side 7.70 s, colour split 7.82 s, matrix-core 14.2 s).  The eight-system
+// forms address a wavefront's systems with 32-bit offsets from the first one's planes and
 // otherwise run the colour split (two systems per block when nr is even; 1, 2 and 4 per
 // block took 8.00, 7.97 and 8.92 s).
 void cg_apply(const ZD* U, const Geom& g, double kappa, double emu, int nr, const CgWork& cw, int adj, int in_field,
               int out_field, int preg, hipStream_t st) {
     const bool fits = (7.0 * kCgFields * cw.fe + g.ldv) * sizeof(ZD) < 4294967296.0;
     const int nb = (np_stencil(g.V) + kXcd - 1) / kXcd * kXcd;
-    if (cw.op == kCgOpTmarch && cg_tm_chunk(g, nr) > 0) {
-        const int T = cg_tm_chunk(g, nr);
-        const int units = g.nx * g.ny * g.nz / kBlock * (g.nt / T);
-        hipLaunchKernelGGL(k_cg_apply_tm, dim3(units * nr), dim3(kBlock), 0, st, U, g, kappa, emu, cw, nr, adj,
-                           in_field, out_field, preg, T);
+    if (cw.op == kCgOpLinks) {
+        // fewest chunks that fill the chip, evenly cut
+        int chunks = std::max((kCgFill + nb - 1) / nb, (nr + kCgChunk - 1) / kCgChunk);
+        chunks = std::min(chunks, nr);
+        const int ns = (nr + chunks - 1) / chunks;
+        hipLaunchKernelGGL(k_cg_apply_links, dim3(nb * ((nr + ns - 1) / ns)), dim3(kCgBlock), 0, st, U, g, kappa, emu,
+                           cw, nr, adj, in_field, out_field, preg, nb / kXcd, ns);
         return;
     }
     if (cw.op == kCgOpMfma && fits) {
@@ -563,7 +566,7 @@ void cg_apply(const ZD* U, const Geom& g, double kappa, double emu, int nr, cons
                            in_field, out_field, preg);
         return;
     }
-    if ((cw.op == kCgOpMulti || cw.op == kCgOpTmarch) && fits) {
+    if (cw.op == kCgOpMulti && fits) {
         hipLaunchKernelGGL(k_cg_apply_mr, dim3(nb, (nr + 7) / 8), dim3(kWave), 0, st, U, g, kappa, emu, cw, nr, adj,
                            in_field, out_field, preg);
         return;
@@ -664,21 +667,22 @@ __global__ __launch_bounds__(kPBlock) void k_cg_init_p(Geom g, CgWork cw, int np
     cw.field(e, kCgP)[i] = cw.field(e, kCgZ)[i];
 }
 
-// alpha = zeta / |A p|^2;  x += alpha p;  r -= alpha w;  partials of |r|^2.
-__global__ __launch_bounds__(kPBlock) void k_cg_update_xr(Geom g, CgWork cw, int npart, int par) {
+// alpha = zeta / |A p|^2;  r -= alpha w;  partials of |r|^2.  x += alpha p waits for the
+// pass that reads p for the next search direction: eight field passes per iteration instead
+// of nine (16^3 x 4, 16 systems: 22 + 33 us at 6.9 and 7.7 TB/s, before 38 + 21 us).
+__global__ __launch_bounds__(kPBlock) void k_cg_update_r(Geom g, CgWork cw, int npart, int par) {
     const int e = blockIdx.z;
     CgRhs* st = cw.st + e;
-    if (block_flag_cg(&st->done)) return;
+    if (*(volatile const int*)&st->done) return;
     double red[1];
     reduce_partials<1, kPBlock>(cw.p(e, 0), npart, red);
     const double alpha = red[0] > 0.0 ? st->zeta[par] / red[0] : 0.0;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) st->alpha = alpha;
     const int s = blockIdx.x * kPBlock + threadIdx.x;
     double v[1] = {0.0};
     if (s < g.V) {
         const size_t i = (size_t)blockIdx.y * g.ldv + s;
-        ZD* x = cw.field(e, kCgX);
         ZD* r = cw.field(e, kCgR);
-        x[i] = x[i] + alpha * cw.field(e, kCgP)[i];
         const ZD rn = r[i] - alpha * cw.field(e, kCgW)[i];
         r[i] = rn;
         v[0] = norm2(rn);
@@ -686,21 +690,35 @@ __global__ __launch_bounds__(kPBlock) void k_cg_update_xr(Geom g, CgWork cw, int
     write_partials_at<1, kPBlock>(cw.p(e, 1), blockIdx.y * gridDim.x + blockIdx.x, v);
 }
 
-// beta = |z_new|^2 / zeta;  p = z + beta p;  zeta_next = |z_new|^2.
-__global__ __launch_bounds__(kPBlock) void k_cg_update_p(Geom g, CgWork cw, int npart, int par) {
+// beta = |z_new|^2 / zeta;  x += alpha p;  p = z + beta p;  zeta_next = |z_new|^2.
+__global__ __launch_bounds__(kPBlock) void k_cg_update_px(Geom g, CgWork cw, int npart, int par) {
     const int e = blockIdx.z;
     CgRhs* st = cw.st + e;
-    if (block_flag_cg(&st->done)) return;
+    if (*(volatile const int*)&st->done) return;
     double red[1];
     reduce_partials<1, kPBlock>(cw.p(e, 2), npart, red);
-    const double zo = st->zeta[par];
+    const double zo = st->zeta[par], alpha = st->alpha;
     const double beta = zo > 0.0 ? red[0] / zo : 0.0;
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) st->zeta[par ^ 1] = red[0];
     const int s = blockIdx.x * kPBlock + threadIdx.x;
     if (s >= g.V) return;
     const size_t i = (size_t)blockIdx.y * g.ldv + s;
+    ZD* x = cw.field(e, kCgX);
     ZD* p = cw.field(e, kCgP);
-    p[i] = cw.field(e, kCgZ)[i] + beta * p[i];
+    const ZD po = p[i];
+    x[i] = x[i] + alpha * po;
+    p[i] = cw.field(e, kCgZ)[i] + beta * po;
+}
+
+// A system froze before its last x += alpha p.
+__global__ __launch_bounds__(kPBlock) void k_cg_last_x(Geom g, CgWork cw) {
+    const int e = blockIdx.z;
+    const CgRhs* st = cw.st + e;
+    const int s = blockIdx.x * kPBlock + threadIdx.x;
+    if (s >= g.V || !st->done || !(st->bnorm2 > 0.0)) return;
+    const size_t i = (size_t)blockIdx.y * g.ldv + s;
+    ZD* x = cw.field(e, kCgX);
+    x[i] = x[i] + st->alpha * cw.field(e, kCgP)[i];
 }
 
 // |r|^2 of every system; converged (|r| <= tol |b|) or stalled systems freeze.
@@ -874,20 +892,24 @@ void launch_cg_start(const ZD* U, const Geom& g, double kappa, double mu, int nr
     const double emu = std::exp(mu);
     cg_apply(U, g, kappa, emu, nr, cw, 1, kCgR, kCgZ, 2, st);
     dim3 gp((g.V + kPBlock - 1) / kPBlock, 12, nr);
-    hipLaunchKernelGGL(k_cg_init_p, gp, dim3(kPBlock), 0, st, g, cw, cg_apply_parts(g, nr, cw.op));
+    hipLaunchKernelGGL(k_cg_init_p, gp, dim3(kPBlock), 0, st, g, cw, np_stencil(g.V));
 }
 
 void launch_cg_iteration(const ZD* U, const Geom& g, double kappa, double mu, int nr, int it, int check, double tol,
                          const CgWork& cw, hipStream_t st) {
     const double emu = std::exp(mu);
     const int par = it & 1;
+    const int npa = np_stencil(g.V);
     const dim3 gp((g.V + kPBlock - 1) / kPBlock, 12, nr);
-    const int npa = cg_apply_parts(g, nr, cw.op);
     cg_apply(U, g, kappa, emu, nr, cw, 0, kCgP, kCgW, 0, st);
-    hipLaunchKernelGGL(k_cg_update_xr, gp, dim3(kPBlock), 0, st, g, cw, npa, par);
+    hipLaunchKernelGGL(k_cg_update_r, gp, dim3(kPBlock), 0, st, g, cw, npa, par);
     if (check) hipLaunchKernelGGL(k_cg_check, dim3(1, nr), dim3(kPBlock), 0, st, cw, np_point(g.V), tol * tol);
     cg_apply(U, g, kappa, emu, nr, cw, 1, kCgR, kCgZ, 2, st);
-    hipLaunchKernelGGL(k_cg_update_p, gp, dim3(kPBlock), 0, st, g, cw, npa, par);
+    hipLaunchKernelGGL(k_cg_update_px, gp, dim3(kPBlock), 0, st, g, cw, npa, par);
+}
+
+void launch_cg_end(const Geom& g, int nr, const CgWork& cw, hipStream_t st) {
+    hipLaunchKernelGGL(k_cg_last_x, dim3((g.V + kPBlock - 1) / kPBlock, 12, nr), dim3(kPBlock), 0, st, g, cw);
 }
 
 void launch_cg_finish(const Geom& g, const ZD* R, const ZD* L, const ZD* c, int l, const CgWork& cw, hipStream_t st) {

@@ -531,7 +531,7 @@ class Context:
 
     def set_cg_operator(self, form: int = 3):
         """Operator form of the deflated derivative's shifted solves: 0 multi-right-hand-side,
-        1 colour split, 2 matrix-core products, 3 t-march (default)."""
+        1 colour split, 2 matrix-core products, 3 links kept over the systems (default)."""
         _check(self.lib, self.lib.tslov_set_cg_operator(self.handle, int(form)))
 
     def pair_ns(self):
