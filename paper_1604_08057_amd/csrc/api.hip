@@ -600,16 +600,12 @@ struct RitzJobs {
     ~RitzJobs() { join(); }
 };
 
-// Largest k whose Ritz summary a sign call forms on the device (one compute unit: 1.0 ms at
-// k = 200 and 2.6 ms at k = 400, against 1.1 and 3.8 ms on host threads; the work grows with
-// k^2, and beyond this one compute unit is no faster than four threads).
-constexpr int kRitzDeviceMax = 512;
-
 // The Ritz summary of a sign call on the device: on a stream of its own, started when the
 // forward pass has ended (the host has waited for it) and joined before the call returns,
 // on every path.  The coefficients it reads are not written in between.
 struct RitzOnDevice {
     tslov_ctx* c;
+    int n = 0;
     bool busy = false;
     explicit RitzOnDevice(tslov_ctx* ctx) : c(ctx) {}
     RitzOnDevice(const RitzOnDevice&) = delete;
@@ -619,17 +615,24 @@ struct RitzOnDevice {
     }
     tslov_status start(int k) {
         if (!c->side) HIPCHK(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
-        CHK(ensure(c->ritz, 3 * sizeof(double)));
+        CHK(ensure(c->ritz, tslov::ritz_bytes(k)));
         tslov::launch_ritz(c->coef.at(0), k, c->ritz.as<double>(), c->side);
         HIPCHK(hipGetLastError());
+        n = k;
         busy = true;
         return TSLOV_OK;
     }
     tslov_status join(tslov::RitzSummary& r) {
         if (!busy) return TSLOV_OK;
         double h[3];
-        HIPCHK(hipMemcpyAsync(h, c->ritz.p, sizeof(h), hipMemcpyDeviceToHost, c->side));
-        HIPCHK(hipStreamSynchronize(c->side));
+        for (int sweeps = tslov::kRitzTopSweeps;;) {
+            HIPCHK(hipMemcpyAsync(h, c->ritz.p, sizeof(h), hipMemcpyDeviceToHost, c->side));
+            HIPCHK(hipStreamSynchronize(c->side));
+            if (h[2] != -2.0) break;
+            sweeps += tslov::kRitzMoreSweeps;
+            tslov::launch_ritz_more(n, c->ritz.as<double>(), sweeps, c->side);
+            HIPCHK(hipGetLastError());
+        }
         busy = false;
         r = tslov::RitzSummary{h[0], h[1], (int)h[2]};
         return TSLOV_OK;
@@ -1315,15 +1318,13 @@ tslov_status sign_impl(tslov_ctx* c, const void* psi_in, void* out, int k, const
     CHK(ensure_work(c, 1, k, 0));
     const SrcList L = make_list({0}, {k});
     std::vector<EntryStatus> es;
-    const bool ritz_here = k <= kRitzDeviceMax;
-    RitzJobs jobs;
-    CHK((forward<R, RL>(c, L, src, nullptr, 0, es, ritz_here ? nullptr : &jobs)));
+    CHK((forward<R, RL>(c, L, src, nullptr, 0, es, nullptr)));
     if (es[0].breakdown == 2)
         return fail(TSLOV_ERR_BREAKDOWN, "serious Lanczos breakdown at step " + std::to_string(es[0].step));
     const double t1 = now_ms();
     const int k_used = es[0].k_used;
     RitzOnDevice ritz(c);
-    if (ritz_here && k_used > 0) CHK(ritz.start(k_used));
+    if (k_used > 0) CHK(ritz.start(k_used));
     SrcList Ld = make_list({0}, {k_used});
     std::vector<int> stag(1, 0);
     if (k_used > 0) {
@@ -1355,10 +1356,6 @@ tslov_status sign_impl(tslov_ctx* c, const void* psi_in, void* out, int k, const
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(c->st));
     CHK(ritz.join(es[0].ritz));
-    if (!ritz_here) {
-        jobs.join();
-        es[0].ritz = jobs.out[0];
-    }
     es[0].flags = entry_flags(c, es[0], stag[0], 0);
     CHK(check_ritz(es[0]));
     const double t3 = now_ms();

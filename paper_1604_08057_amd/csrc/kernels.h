@@ -347,8 +347,13 @@ struct RatWork {
 void launch_ratsign(Coef coef, const SrcList& L, const RatWork& w, int N, hipStream_t st);
 
 // out[0] = min |Re theta| over the eigenvalues theta of T_k (slot 0's coefficients, k <= 1024),
-// out[1] = its infinity norm, out[2] = sweeps of the last stage (-1: some root unsettled).
+// out[1] = its infinity norm, out[2] = sweeps of the last stage (-1: some root unsettled; -2:
+// some root still open, launch_ritz_more).  out: ritz_bytes(k) bytes.
+size_t ritz_bytes(int k);
 void launch_ritz(Coef coef, int k, double* out, hipStream_t st);
+// more sweeps at the full size, `sweeps` of them in all then
+constexpr int kRitzTopSweeps = 16, kRitzMoreSweeps = 32;
+void launch_ritz_more(int k, double* out, int sweeps, hipStream_t st);
 
 // c = X e_1, adjoint seeds from Y, S = |x| Re sum_j c_j h_j.
 void launch_dense_extract(Coef coef, const SrcList& L, int grad, const DenseWork& w, hipStream_t st);
