@@ -471,9 +471,16 @@ const Z<RL>* links(const tslov_ctx* c) {
 // Device bytes one source of up to kcap steps needs (workspace sizing).
 // Chunks of steps the force contraction splits each entry into (its partials are
 // summed afterwards): about 2^18 threads in all, and at least 16 chunks so that a
-// large lattice does not leave each thread a loop over every step.  A function of
-// the lattice only, so an entry's result does not depend on its batch.
-int force_chunks(int V) { return std::max(16, std::min((1 << 18) / (4 * V), 64)); }
+// large lattice does not leave each thread a loop over every step.  A segment of m
+// steps (0: every vector stored) gets about five steps per chunk if that leaves enough
+// threads: each chunk adds its partial to memory once per segment (16^4, segments of
+// 20 steps, 1, 2, 4, 8, 16 chunks: 456, 451, 448, 487 and 605 us per segment, the sum
+// over them 21 to 140 us).  A function of the lattice and the segment only, so an
+// entry's result does not depend on its batch.
+int force_chunks(int V, int m) {
+    const int fill = std::min((1 << 18) / (4 * V), 64), whole = std::max(16, fill);
+    return m > 0 ? std::min(whole, std::max({fill, (m + 4) / 5, 1})) : whole;
+}
 
 size_t bytes_per_source(const tslov_ctx* c, int kcap, int grad, int m = 0) {
     const size_t fb = c->field_bytes();
@@ -483,7 +490,7 @@ size_t bytes_per_source(const tslov_ctx* c, int kcap, int grad, int m = 0) {
     b += (size_t)tslov::kNP * c->pstride() * sizeof(double) + coef_bytes(1, kcap);
     b += (size_t)6 * kcap * kcap * sizeof(ZD) + (size_t)tslov::dense_pstride(kcap) * sizeof(double);
     if (grad)
-        b += (size_t)(force_chunks(c->g.V) + 1) * 36 * c->g.ldv * sizeof(ZD) + (size_t)2 * 12 * c->g.V * sizeof(ZD);
+        b += (size_t)(force_chunks(c->g.V, m) + 1) * 36 * c->g.ldv * sizeof(ZD) + (size_t)2 * 12 * c->g.V * sizeof(ZD);
     return b;
 }
 
@@ -1099,9 +1106,9 @@ tslov_status backward(tslov_ctx* c, const SrcList& L, GradOut& out) {
     const int m = c->ring ? c->ring_m : 0;
     if (m && out.ward) return fail(TSLOV_ERR_ARG, "the Ward check needs every Krylov vector stored");
     // force contraction split in chunks of j for parallelism; the split depends on
-    // the lattice (and the segment) only, so a source's result does not depend on
+    // the lattice and the segment only, so a source's result does not depend on
     // the batch it shares a launch with
-    const int nchunk = force_chunks(g.V);
+    const int nchunk = force_chunks(g.V, m);
     CHK(ensure(c->gpart, (size_t)c->slots * nchunk * 36 * g.ldv * sizeof(ZD)));
     int nlt = 0;   // entries with k_used > j form a prefix
     PairTuner tune(c, 1, L.n);
