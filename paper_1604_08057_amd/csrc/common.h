@@ -539,6 +539,28 @@ __device__ __forceinline__ void gather_partials(const double* __restrict__ part,
         for (int i = 0; i < NV; ++i) out[i] += part[b * NV + i];
 }
 
+// gather_partials with the loads of U partials out at once, added in the same order (a slot
+// past the end adds 0.0, which changes no bit of a sum that starts at 0.0).
+template <int NV, int BLK, int U>
+__device__ __forceinline__ void gather_partials_deep(const double* __restrict__ part, int nparts, double (&out)[NV]) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) out[i] = 0.0;
+#pragma unroll 1
+    for (int b = threadIdx.x; b < nparts; b += U * BLK) {
+        double t[U][NV];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const double* const q = part + min(b + u * BLK, nparts - 1) * NV;
+#pragma unroll
+            for (int i = 0; i < NV; ++i) t[u][i] = q[i];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < NV; ++i) out[i] += b + u * BLK < nparts ? t[u][i] : 0.0;
+    }
+}
+
 template <int NV, int BLK>
 __device__ __forceinline__ void reduce_partials(const double* __restrict__ part, int nparts, double (&out)[NV]) {
     gather_partials<NV, BLK>(part, nparts, out);

@@ -324,6 +324,134 @@ __device__ __forceinline__ void hop_all_pair_x(Z<R> (&acca)[NS][4], Z<R> (&accb)
     }
 }
 
+// Pair hops with a wavefront per direction.  A block of four wavefronts owns 64 sites;
+// wavefront nu takes both hops of direction nu for every colour, its two links in registers
+// over both fields, one neighbour spinor in flight while the other is multiplied, and leaves
+// the link-applied half spinors in LDS.  After a barrier wavefront a < 3 adds the eight hops
+// of colour a in the order of the other forms.  The link-row products are row_dot's chain,
+// so an entry gets the bits of the other forms.  Bound by latency: one round trip per
+// neighbour spinor and the epilogue's, with two workgroups per compute unit (held to three,
+// 18 registers spill and 16^4 with float32 links takes 38 us instead of 31).
+constexpr int kDBlock = 4 * kSites;
+
+// Where the direction split serves a launch of n one-entry float64 workgroups per site
+// block, instead of the colour split: the 512 workgroups that are resident at once (two per
+// compute unit, by LDS and registers) must not leave the last round mostly empty, which the
+// colour split's four per compute unit avoid; and a long batch is bound by its traffic, where
+// the colour split's occupancy does better.  Forward and reverse pair in us, colour split to
+// direction split: 12^4 (324 site blocks) 18.8, 24.2 -> 16.7, 22.0; 16^4 (1024) 45.0, 58.4 ->
+// 41.2, 50.2, with float32 links 40.8, 58.4 -> 31, 54; 16^3 x 32 (2048) 85, 135 -> 78, 124;
+// 8 entries of 10^4 (1256) 37.4, 48.0 -> 35.0, 44.7; but 14^4 (601) 26.6, 34.2 -> 27.9, 37.2
+// and 6 entries of 18^3 x 6 (3282) 78.8, 111 -> 80.9, 115.  float32 fields: no gain.
+inline bool direction_split(const Geom& g, int n) {
+    const long long b = (long long)np_stencil(g.V) * n, slots = 512, rounds = (b + slots - 1) / slots;
+    if (n > 1 && rounds > 4) return false;
+    return rounds == 1 || 4 * b >= 3 * slots * rounds;
+}
+
+template <typename R>
+using DirTile = Z<R>[4][12][kSites];   // direction; forward, backward x half spin x colour; site
+
+template <typename R>
+__device__ __forceinline__ void dir_load(Spinor<R>& p, const Z<R>* __restrict__ f, int ldv, unsigned y) {
+    const FieldBase b = field_base(f);
+#pragma unroll
+    for (int sp = 0; sp < 4; ++sp)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) p.c[sp][c] = fload<R>(b, ldv, sp * 3 + c, y);
+}
+
+template <typename R>
+__device__ __forceinline__ void dir_put(Z<R> (*t)[kSites], const Z<R> (&u)[3][3], const Z<R> (&h)[2][3]) {
+    const int l = threadIdx.x % kSites;
+#pragma unroll
+    for (int sp = 0; sp < 2; ++sp)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) t[sp * 3 + c][l] = row_dot(u[c], h[sp][0], h[sp][1], h[sp][2]);
+}
+
+template <int NU, typename R>
+__device__ __forceinline__ void dir_add(Z<R> (&acc)[4], const Z<R> (*t)[kSites], int a, int l, R cf, R cb) {
+    const Z<R> of[2] = {t[a][l], t[3 + a][l]}, ob[2] = {t[6 + a][l], t[9 + a][l]};
+    recon1_add<NU, +1>(acc, of, cf);
+    recon1_add<NU, -1>(acc, ob, cb);
+}
+
+// The hop sum of colour W (the fourth wavefront has none), with up and dn the factors of the
+// forward and backward t-hop.
+template <int W, typename R>
+__device__ __forceinline__ void dir_sum(Z<R> (&acc)[4], const DirTile<R>& t, R up, R dn) {
+    zero1(acc);
+    if (W == 3) return;
+    const int l = threadIdx.x % kSites;
+    dir_add<0>(acc, t[0], W, l, R(1), R(1));
+    dir_add<1>(acc, t[1], W, l, R(1), R(1));
+    dir_add<2>(acc, t[2], W, l, R(1), R(1));
+    dir_add<3>(acc, t[3], W, l, up, dn);
+}
+
+template <int W, typename R, typename RL, typename Before>
+__device__ __forceinline__ void dir_pair_wave(Z<R> (&acca)[4], Z<R> (&accb)[4], DirTile<R>& t,
+                                              const Z<RL>* __restrict__ U, const Z<R>* __restrict__ fa,
+                                              const Z<R>* __restrict__ fb, const Geom& g, int s, R ep, R em,
+                                              Before before) {
+    const Nbr n = neighbours(g, s);
+    const unsigned yf = (unsigned)n.fwd[W], yb = (unsigned)n.bwd[W];
+    const FieldBase u = field_base(U);
+    Spinor<R> pf, pb;
+    Z<R> uf[3][3], ub[3][3], h[2][3];   // ub: rows of U^dag(x - nu)
+    dir_load(pf, fa, g.ldv, yf);
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) uf[a][b] = zcast<R>(fload<RL>(u, g.ldv, W * 9 + a * 3 + b, (unsigned)s));
+    mem_fence_compiler();
+    before();
+    mem_fence_compiler();
+    dir_load(pb, fa, g.ldv, yb);
+    project<W, +1>(pf, h);
+    dir_put(t[W], uf, h);
+    mem_fence_compiler();
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) ub[b][a] = cj(zcast<R>(fload<RL>(u, g.ldv, W * 9 + a * 3 + b, yb)));
+    project<W, -1>(pb, h);
+    mem_fence_compiler();
+    dir_load(pf, fb, g.ldv, yf);
+    mem_fence_compiler();
+    dir_put(t[W] + 6, ub, h);
+    mem_fence_compiler();
+    __syncthreads();
+    dir_sum<W>(acca, t, ep, em);
+    project<W, +1>(pf, h);
+    mem_fence_compiler();
+    dir_load(pb, fb, g.ldv, yb);
+    mem_fence_compiler();
+    __syncthreads();   // the sums are read before the second field's hops come
+    dir_put(t[W], uf, h);
+    project<W, -1>(pb, h);
+    dir_put(t[W] + 6, ub, h);
+    mem_fence_compiler();
+    __syncthreads();
+    dir_sum<W>(accb, t, em, ep);
+}
+
+// Hop sums of fields fa (at +mu) and fb (at -mu) at site s, colour w of wavefronts w < 3.
+// Every thread of the block calls it; s is a site of the lattice.  before() runs behind the
+// first loads.
+template <typename R, typename RL, typename Before>
+__device__ __forceinline__ void dir_pair(Z<R> (&acca)[4], Z<R> (&accb)[4], DirTile<R>& t, const Z<RL>* __restrict__ U,
+                                         const Z<R>* __restrict__ fa, const Z<R>* __restrict__ fb, const Geom& g,
+                                         int s, int w, R ep, R em, Before before) {
+    switch (w) {
+        case 0: dir_pair_wave<0>(acca, accb, t, U, fa, fb, g, s, ep, em, before); break;
+        case 1: dir_pair_wave<1>(acca, accb, t, U, fa, fb, g, s, ep, em, before); break;
+        case 2: dir_pair_wave<2>(acca, accb, t, U, fa, fb, g, s, ep, em, before); break;
+        default: dir_pair_wave<3>(acca, accb, t, U, fa, fb, g, s, ep, em, before); break;
+    }
+}
+
 // Block-uniform reads of the stop flags of NS entries (1 for an entry past the
 // end of the list), with one pair of barriers for all of them.
 template <int NS>
@@ -994,6 +1122,48 @@ __global__ __launch_bounds__(kCBlock) void k_fwd_pair_ms(const Z<RL>* __restrict
     }
 }
 
+// Direction split (see direction_split): one entry per workgroup; the partial-sum slot is the
+// site block.
+template <typename R, typename RL>
+__global__ __launch_bounds__(kDBlock, 2) void k_fwd_pair_dirs(const Z<RL>* __restrict__ U, Geom g, double kappa,
+                                                              double emu, Work<R> wk, SrcList L, Coef coef0, int j,
+                                                              int npart_in, int has_eta, int replay) {
+    __shared__ DirTile<R> hops;
+    __shared__ double part[3][kNvRecur];
+    __shared__ int stop;
+    const int sb = sten_block<kCBlock>(g);
+    if (sb < 0) return;   // padding workgroup (uniform over the block)
+    const int slot = L.slot[blockIdx.y];
+    const Z<R>* const rin = wk.f(slot, j == 1 ? 0 : 2);
+    const Z<R>* const sin = wk.f(slot, j == 1 ? 0 : 3);
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kSites), l = threadIdx.x % kSites;
+    const int s = sb * kSites + l;
+    if (threadIdx.x == 0) stop = *(volatile const int*)coef0.at(slot).status;   // read behind the hops' barriers
+    // the previous step's sums, thread by thread as the other forms gather them
+    const auto sums = [&]() {
+        if (replay) return;
+        if (w < 3) {
+            double red[kNvRecur];
+            gather_partials_deep<kNvRecur, kCBlock, 4>(wk.p(slot, 1), npart_in, red);
+#pragma unroll
+            for (int i = 0; i < kNvRecur; ++i) {
+                const double v = wave_sum(red[i]);
+                if (l == 0) part[w][i] = v;
+            }
+        }
+    };
+    Z<R> acca[4], accb[4];
+    dir_pair(acca, accb, hops, U, rin, sin, g, min(s, g.V - 1), w, (R)emu, (R)(1.0 / emu), sums);
+    mem_fence_compiler();
+    if (!replay && __builtin_amdgcn_readfirstlane(stop)) return;
+    double red[kNvRecur] = {0.0, 0.0, 0.0, 0.0};
+    if (!replay)
+#pragma unroll
+        for (int i = 0; i < kNvRecur; ++i) red[i] = ((0.0 + part[0][i]) + part[1][i]) + part[2][i];
+    fwd_pair_finish<R, kDBlock>(g, kappa, wk, coef0.at(slot), slot, j, sb, min(w, 2), w < 3 ? s : g.V, red, acca, accb,
+                                rin, sin, has_eta, replay);
+}
+
 template <typename R, typename RL>
 void fwd_pair_launch(const Z<RL>* U, const Geom& g, double kappa, double mu, const Work<R>& wk, const SrcList& L,
                      Coef coef, int j, int has_eta, int ns, int replay, hipStream_t st, Timing t) {
@@ -1015,6 +1185,12 @@ void fwd_pair_launch(const Z<RL>* U, const Geom& g, double kappa, double mu, con
                          j, npart_in, has_eta, replay);
             break;
         default:
+            if constexpr (sizeof(R) == sizeof(double))
+                if (direction_split(g, L.n)) {
+                    timed_launch(k_fwd_pair_dirs<R, RL>, dim3(g.nwg, L.n), dim3(kDBlock), st, t, U, g, kappa, emu, wk, L,
+                                 coef, j, npart_in, has_eta, replay);
+                    return;
+                }
             timed_launch(k_fwd_pair_ms<R, 1, RL>, dim3(g.nwg, L.n), block, st, t, U, g, kappa, emu, wk, L, coef, j,
                          npart_in, has_eta, replay);
     }
@@ -1489,7 +1665,7 @@ __global__ __launch_bounds__(kPBlock) void k_bwd_ra(Geom g, Work<R> wk, SrcList 
     const double bbar_n = coef.bbar_tot[j + 1];
     const ZD gbar_n = coef.gbar_tot[j + 1];
     double red[kNvRB];
-    gather_partials<kNvRB, kPBlock>(wk.p(slot, 0), npart_in, red);   // its loads join the operands'
+    gather_partials_deep<kNvRB, kPBlock, 4>(wk.p(slot, 0), npart_in, red);   // its loads join the operands'
     block_sum_last<kNvRB, kPBlock>(red);
     const double D1 = red[0];
     const ZD D2 = mk<double>(red[1], red[2]);
@@ -1879,6 +2055,41 @@ __global__ __launch_bounds__(kCBlock) void k_bwd_rb_ms(const Z<RL>* __restrict__
     }
 }
 
+// Direction split (see direction_split), not the last step: one entry per workgroup.
+template <typename R, typename RL>
+__global__ __launch_bounds__(kDBlock, 2) void k_bwd_rb_dirs(const Z<RL>* __restrict__ U, Geom g, double kappa,
+                                                            double emu, Work<R> wk, SrcList L, Coef coef0, int j,
+                                                            int npart_in) {
+    __shared__ DirTile<R> hops;
+    __shared__ double part[3][kNvRA];
+    const int sb = sten_block<kCBlock>(g);
+    if (sb < 0) return;   // padding workgroup (uniform over the block)
+    const int e = blockIdx.y, slot = L.slot[e];
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kSites), l = threadIdx.x % kSites;
+    const int s = sb * kSites + l;
+    const BwdCoefs cf = bwd_coefs(coef0.at(slot), j, j + 1 < L.k[e]);
+    // the step's sums, thread by thread as the other forms gather them
+    const auto sums = [&]() {
+        if (w == 3) return;
+        double red[kNvRA];
+        gather_partials_deep<kNvRA, kCBlock, 4>(wk.p(slot, 1), npart_in, red);
+#pragma unroll
+        for (int i = 0; i < kNvRA; ++i) {
+            const double v = wave_sum(red[i]);
+            if (l == 0) part[w][i] = v;
+        }
+    };
+    Z<R> accs[4], accr[4];
+    dir_pair(accs, accr, hops, U, (const Z<R>*)wk.sb(slot, j), (const Z<R>*)wk.f(slot, 6 + (j & 1)), g, min(s, g.V - 1),
+             w, (R)emu, (R)(1.0 / emu), sums);
+    mem_fence_compiler();
+    double red[kNvRA];
+#pragma unroll
+    for (int i = 0; i < kNvRA; ++i) red[i] = ((0.0 + part[0][i]) + part[1][i]) + part[2][i];
+    bwd_rb_finish<R, false, kDBlock>(g, kappa, wk, coef0.at(slot), slot, j, L.k[e], sb, min(w, 2), w < 3 ? s : g.V, red,
+                                     accs, accr, cf);
+}
+
 template <typename R, typename RL>
 void launch_bwd_rb(const Z<RL>* U, const Geom& g, double kappa, double mu, const Work<R>& wk, const SrcList& L,
                    Coef coef, int j, int last, int ns, hipStream_t st, Timing t) {
@@ -1898,8 +2109,15 @@ void launch_bwd_rb(const Z<RL>* U, const Geom& g, double kappa, double mu, const
     else if (ns == 2)
         timed_launch(k_bwd_rb_ms<R, 2, RL>, dim3(g.nwg, (L.n + 1) / 2), dim3(kCBlock), st, t, U, g, kappa, emu, wk, L,
                      coef, j, np);
-    else
+    else {
+        if constexpr (sizeof(R) == sizeof(double))
+            if (direction_split(g, L.n)) {
+                timed_launch(k_bwd_rb_dirs<R, RL>, dim3(g.nwg, L.n), dim3(kDBlock), st, t, U, g, kappa, emu, wk, L, coef,
+                             j, np);
+                return;
+            }
         timed_launch(k_bwd_rb_ms<R, 1, RL>, dim3(g.nwg, L.n), dim3(kCBlock), st, t, U, g, kappa, emu, wk, L, coef, j, np);
+    }
 }
 
 // =============================================================== force contraction
