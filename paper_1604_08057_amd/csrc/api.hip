@@ -378,7 +378,7 @@ tslov_status ensure_host_part(tslov_ctx* c, int n) {
 // ---------------------------------------------------------------- batch workspace
 size_t coef_bytes(int slots, int kcap) {
     const size_t n = (size_t)kcap + 2;
-    return (size_t)slots * (n * (7 * sizeof(ZD) + 4 * sizeof(double)) + 16 * sizeof(int) + 16 * sizeof(double));
+    return (size_t)slots * (n * (8 * sizeof(ZD) + 5 * sizeof(double)) + 16 * sizeof(int) + 16 * sizeof(double));
 }
 
 void carve_coef(tslov_ctx* c, int slots, int kcap) {
@@ -397,7 +397,9 @@ void carve_coef(tslov_ctx* c, int slots, int kcap) {
     cf.abar_T = (ZD*)take(S * n * sizeof(ZD));
     cf.gbar_T = (ZD*)take(S * n * sizeof(ZD));
     cf.gbar_tot = (ZD*)take(S * n * sizeof(ZD));
+    cf.icg = (ZD*)take(S * n * sizeof(ZD));
     cf.beta = (double*)take(S * n * sizeof(double));
+    cf.ib = (double*)take(S * n * sizeof(double));
     cf.anorm2 = (double*)take(S * n * sizeof(double));
     cf.bbar_T = (double*)take(S * n * sizeof(double));
     cf.bbar_tot = (double*)take(S * n * sizeof(double));
@@ -657,7 +659,7 @@ tslov_status check_ritz(const EntryStatus& s) {
 }
 
 // Recompute mode: the state before forward step j0 = 1 + seg m of every entry of
-// L (the residuals r, s of step j0 - 1 and v_{j0-1}, w_{j0-1}), saved (restore = 0)
+// L (the residuals of steps j0 - 1 and j0 - 2, from which v, w follow), saved (restore = 0)
 // to or restored (restore = 1) from checkpoint seg of the entry's slot.
 template <typename R>
 tslov_status checkpoint(tslov_ctx* c, const SrcList& L, int seg, int j0, int restore) {
@@ -667,7 +669,7 @@ tslov_status checkpoint(tslov_ctx* c, const SrcList& L, int seg, int j0, int res
     for (int e = 0; e < L.n; ++e) {
         const int slot = L.slot[e];
         char* base = c->ckpt.as<char>() + ((size_t)slot * nseg + seg) * 4 * fb;
-        void* live[4] = {wk.f(slot, 2), wk.f(slot, 3), wk.v(slot, j0 - 1), wk.w(slot, j0 - 1)};
+        void* live[4] = {wk.v(slot, j0), wk.w(slot, j0), wk.v(slot, j0 - 1), wk.w(slot, j0 - 1)};
         for (int i = 0; i < 4; ++i) {
             void* saved = base + (size_t)i * fb;
             HIPCHK(hipMemcpyAsync(restore ? live[i] : saved, restore ? saved : live[i], fb, hipMemcpyDeviceToDevice,
@@ -1148,7 +1150,7 @@ tslov_status backward(tslov_ctx* c, const SrcList& L, GradOut& out) {
         } else {
             CHK(loop());
         }
-        tslov::launch_force<R>(g, c->kappa, c->mu, wk, L, nchunk, c->gpart.as<ZD>(), c->st);
+        tslov::launch_force<R>(g, c->kappa, c->mu, wk, L, c->coef, nchunk, c->gpart.as<ZD>(), c->st);
     } else {
         tslov::launch_zero(c->gpart.as<double>(), (size_t)c->slots * nchunk * 72 * g.ldv, c->st);
         for (int seg = n_segments(kmax, m) - 1; seg >= 0; --seg) {
@@ -1162,7 +1164,7 @@ tslov_status backward(tslov_ctx* c, const SrcList& L, GradOut& out) {
             // the segment's share of y = |x| sum_j c_j v_j while its vectors are in the ring
             if (out.y) tslov::launch_assemble<R>(g, wk, reaching(j0), c->coef, nullptr, 0, out.y, c->st, j0, j1);
             for (int j = j1; j >= j0; --j) reverse_step(j);
-            tslov::launch_force<R>(g, c->kappa, c->mu, wk, reaching(j0), nchunk, c->gpart.as<ZD>(), c->st, j0, j1,
+            tslov::launch_force<R>(g, c->kappa, c->mu, wk, reaching(j0), c->coef, nchunk, c->gpart.as<ZD>(), c->st, j0, j1,
                                    1);
         }
     }

@@ -451,6 +451,31 @@ __device__ __forceinline__ void force_pair(ZD (&G)[3][3], const Spinor<R>& p_x, 
         }
 }
 
+// force_pair with p to be multiplied by ef (its part at x) and eb (at x + nu), complex.
+template <int NU, typename R>
+__device__ __forceinline__ void force_pair_scaled(ZD (&G)[3][3], const Spinor<R>& p_x, const Spinor<R>& q_x,
+                                                  const Spinor<R>& p_y, const Spinor<R>& q_y, ZD ef, ZD eb) {
+    Spinor<R> gp_x = p_x, gp_y = p_y;
+    g5_inplace(gp_x);
+    g5_inplace(gp_y);
+    Z<R> hP[2][3], hQ[2][3], hP2[2][3], hQ2[2][3];
+    project<NU, +1>(gp_x, hP);
+    project<NU, +1>(q_y, hQ);
+    project<NU, -1>(gp_y, hP2);
+    project<NU, -1>(q_x, hQ2);
+#pragma unroll
+    for (int sp = 0; sp < 2; ++sp)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const ZD f = ef * zcast<double>(hP[sp][a]), b2 = eb * zcast<double>(hP2[sp][a]);
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                G[a][b] = G[a][b] + mulcj(f, zcast<double>(hQ[sp][b]));
+                G[b][a] = G[b][a] + mulcj(zcast<double>(hQ2[sp][b]), b2);
+            }
+        }
+}
+
 // ------------------------------------------------------------------ reductions
 // Cross-lane moves of a double: DPP within rows of 16 lanes, lane reads across rows.
 template <int CTRL>
@@ -621,6 +646,8 @@ __device__ __forceinline__ double spinor_norm2(const Spinor<R>& a) {
 struct Coef {
     ZD* alpha;      // alpha_j = w_j^H H v_j
     double* beta;   // beta_j (beta_1 = |x|)
+    double* ib;     // 1 / beta_j: v_j = ib_j r_j
+    ZD* icg;        // 1 / conj(gamma_j): w_j = icg_j s_j
     ZD* gamma;      // gamma_j (gamma_1 = |x|)
     double* anorm2; // |H v_j|^2
     ZD* h;          // eta^H v_j (derivative mode)
@@ -639,7 +666,7 @@ struct Coef {
     __host__ __device__ Coef at(int slot) const {
         Coef o = *this;
         const size_t d = (size_t)slot * n, m = (size_t)slot * 16;
-        o.alpha += d; o.beta += d; o.gamma += d; o.anorm2 += d; o.h += d; o.c += d;
+        o.alpha += d; o.beta += d; o.ib += d; o.icg += d; o.gamma += d; o.anorm2 += d; o.h += d; o.c += d;
         o.abar_T += d; o.bbar_T += d; o.gbar_T += d; o.bbar_tot += d; o.gbar_tot += d;
         o.status += m; o.misc += m;
         return o;

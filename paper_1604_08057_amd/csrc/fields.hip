@@ -819,6 +819,23 @@ __device__ __forceinline__ void wave_partials_at(double* __restrict__ part, int 
         for (int i = 0; i < NV; ++i) part[slot * NV + i] = v[i];
 }
 
+// The basis is held unnormalised, as the recurrence leaves it: v_j = ib_j r_j and w_j =
+// icg_j s_j are formed where they are read, by fixed fused multiply-adds, so that every
+// reader has the bits the pair kernel's sums were formed with.  That leaves the pair kernel
+// two fields to store instead of four (pair and recurrence at 18^3 x 6, 6 sources: 79 + 45 us
+// -> 75 + 45; 14^4: 25 + 14.4 -> 23.6 + 14.4; 8^4: 7.0 + 5.3 -> 6.7 + 4.8).
+template <typename R>
+struct BasisScale {
+    R ib;
+    Z<R> icg;
+    __device__ __forceinline__ BasisScale(R b, Z<R> g) : ib(b), icg(g) {}
+    __device__ __forceinline__ BasisScale(const Coef& c, int j) : ib((R)c.ib[j]), icg(zcast<R>(c.icg[j])) {}
+    __device__ __forceinline__ Z<R> v(Z<R> r) const { return ib * r; }
+    __device__ __forceinline__ Z<R> w(Z<R> s) const {
+        return mk<R>(fmadd(icg.re, s.re, -(icg.im * s.im)), fmadd(icg.im, s.re, icg.re * s.im));
+    }
+};
+
 // Epilogue of step j for one entry, after the hops: breakdown decisions from the
 // block-summed previous (omega, |r|^2, |s|^2) in `red`, the coefficient records,
 // the stores of v_j, w_j, a_j, b_j and the step's partial sums.  Every branch
@@ -875,8 +892,14 @@ __device__ __forceinline__ void fwd_pair_finish(const Geom& g, double kappa, con
         if (first) coef.misc[0] = beta;
     }
     }
-    const R ib = (R)(1.0 / beta);
-    const Z<R> icg = zcast<R>(zdiv(mk<double>(1.0, 0.0), cj(gam)));
+    const double ibd = 1.0 / beta;
+    const ZD icgd = zdiv(mk<double>(1.0, 0.0), cj(gam));
+    if (!replay && blockIdx.x == 0 && threadIdx.x == 0) {
+        coef.ib[j] = ibd;
+        coef.icg[j] = icgd;
+    }
+    const R ib = (R)ibd;
+    const Z<R> icg = zcast<R>(icgd);
     double pv[kNvPair] = {0.0, 0.0, 0.0, 0.0, 0.0};
     if (s < g.V) {
         Z<R> r0[4], s0[4], v[4], w[4], av[4], bv[4];
@@ -887,7 +910,7 @@ __device__ __forceinline__ void fwd_pair_finish(const Geom& g, double kappa, con
         for (int sp = 0; sp < 4; ++sp) {
             const R sg = sp < 2 ? R(1) : R(-1);
             v[sp] = ib * r0[sp];
-            w[sp] = icg * s0[sp];
+            w[sp] = BasisScale<R>(ib, icg).w(s0[sp]);
             av[sp] = (sg * ib) * (r0[sp] - kap * acca[sp]);
             bv[sp] = icg * (sg * (s0[sp] - kap * accb[sp]));
             const ZD wd = zcast<double>(w[sp]), ad = zcast<double>(av[sp]);
@@ -896,8 +919,10 @@ __device__ __forceinline__ void fwd_pair_finish(const Geom& g, double kappa, con
             pv[1] += wa.im;
             pv[2] += norm2(ad);
         }
-        store1_nt(wk.v(slot, j), g.ldv, a, s, v);
-        store1_nt(wk.w(slot, j), g.ldv, a, s, w);
+        if (first) {   // the source is both first residuals
+            store1_nt(wk.v(slot, j), g.ldv, a, s, r0);
+            store1_nt(wk.w(slot, j), g.ldv, a, s, s0);
+        }
         store1_nt(wk.a(slot, j), g.ldv, a, s, av);
         store1_nt(wk.b(slot, j), g.ldv, a, s, bv);
         if (!replay && has_eta) {
@@ -967,8 +992,14 @@ __device__ __forceinline__ void fwd_pair_finish_pre(const Geom& g, double kappa,
         if (first) coef.misc[0] = beta;
     }
     }
-    const R ib = (R)(1.0 / beta);
-    const Z<R> icg = zcast<R>(zdiv(mk<double>(1.0, 0.0), cj(gam)));
+    const double ibd = 1.0 / beta;
+    const ZD icgd = zdiv(mk<double>(1.0, 0.0), cj(gam));
+    if (!replay && blockIdx.x == 0 && threadIdx.x == 0) {
+        coef.ib[j] = ibd;
+        coef.icg[j] = icgd;
+    }
+    const R ib = (R)ibd;
+    const Z<R> icg = zcast<R>(icgd);
     double pv[kNvPair] = {0.0, 0.0, 0.0, 0.0, 0.0};
     if (s < g.V) {
         Z<R> v[4], w[4], av[4], bv[4];
@@ -977,7 +1008,7 @@ __device__ __forceinline__ void fwd_pair_finish_pre(const Geom& g, double kappa,
         for (int sp = 0; sp < 4; ++sp) {
             const R sg = sp < 2 ? R(1) : R(-1);
             v[sp] = ib * r0[sp];
-            w[sp] = icg * s0[sp];
+            w[sp] = BasisScale<R>(ib, icg).w(s0[sp]);
             av[sp] = (sg * ib) * (r0[sp] - kap * acca[sp]);
             bv[sp] = icg * (sg * (s0[sp] - kap * accb[sp]));
             const ZD wd = zcast<double>(w[sp]), ad = zcast<double>(av[sp]);
@@ -986,8 +1017,10 @@ __device__ __forceinline__ void fwd_pair_finish_pre(const Geom& g, double kappa,
             pv[1] += wa.im;
             pv[2] += norm2(ad);
         }
-        store1_nt(wk.v(slot, j), g.ldv, a, s, v);
-        store1_nt(wk.w(slot, j), g.ldv, a, s, w);
+        if (first) {   // the source is both first residuals
+            store1_nt(wk.v(slot, j), g.ldv, a, s, r0);
+            store1_nt(wk.w(slot, j), g.ldv, a, s, s0);
+        }
         store1_nt(wk.a(slot, j), g.ldv, a, s, av);
         store1_nt(wk.b(slot, j), g.ldv, a, s, bv);
         if (!replay && has_eta) {
@@ -1021,8 +1054,8 @@ void k_fwd_pair(const Z<RL>* __restrict__ U, Geom g, double kappa, double emu, W
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kSites);
     const int slot = L.slot[blockIdx.y];
     const int first = j == 1;
-    const Z<R>* rin = wk.f(slot, first ? 0 : 2);
-    const Z<R>* sin = wk.f(slot, first ? 0 : 3);
+    const Z<R>* rin = first ? wk.f(slot, 0) : wk.v(slot, j);
+    const Z<R>* sin = first ? wk.f(slot, 0) : wk.w(slot, j);
     const int ncb = gridDim.x / 3;   // colour-major grid, as sten_block / sten_colour for the colour grid
     const int sb = blockIdx.x % ncb, a = blockIdx.x / ncb;
     const int l = threadIdx.x % kSites;
@@ -1084,8 +1117,8 @@ __global__ __launch_bounds__(kCBlock) void k_fwd_pair_ms(const Z<RL>* __restrict
 #pragma unroll
     for (int q = 0; q < NS; ++q) {
         slot[q] = L.slot[min(e0 + q, L.n - 1)];
-        rin[q] = wk.f(slot[q], first ? 0 : 2);
-        sin[q] = wk.f(slot[q], first ? 0 : 3);
+        rin[q] = first ? wk.f(slot[q], 0) : wk.v(slot[q], j);
+        sin[q] = first ? wk.f(slot[q], 0) : wk.w(slot[q], j);
 #pragma unroll
         for (int i = 0; i < kNvRecur; ++i) red[q][i] = 0.0;
         if (!replay) gather_partials<kNvRecur, kCBlock>(wk.p(slot[q], 1), npart_in, red[q]);
@@ -1134,8 +1167,8 @@ __global__ __launch_bounds__(kDBlock, 2) void k_fwd_pair_dirs(const Z<RL>* __res
     const int sb = sten_block<kCBlock>(g);
     if (sb < 0) return;   // padding workgroup (uniform over the block)
     const int slot = L.slot[blockIdx.y];
-    const Z<R>* const rin = wk.f(slot, j == 1 ? 0 : 2);
-    const Z<R>* const sin = wk.f(slot, j == 1 ? 0 : 3);
+    const Z<R>* const rin = j == 1 ? wk.f(slot, 0) : wk.v(slot, j);
+    const Z<R>* const sin = j == 1 ? wk.f(slot, 0) : wk.w(slot, j);
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kSites), l = threadIdx.x % kSites;
     const int s = sb * kSites + l;
     if (threadIdx.x == 0) stop = *(volatile const int*)coef0.at(slot).status;   // read behind the hops' barriers
@@ -1238,6 +1271,7 @@ __global__ __launch_bounds__(kPBlock) void k_recur(Geom g, Work<R> wk, SrcList L
     // ahead of the flag test)
     const Z<R> gj = has_prev ? zcast<R>(coef.gamma[j]) : mk<R>(0, 0);
     const R bj = has_prev ? (R)coef.beta[j] : R(0);
+    const BasisScale<R> sj(coef, j), sp(coef, has_prev ? j - 1 : j);
     Z<R> a_i = mk<R>(0, 0), b_i = a_i, v_i = a_i, w_i = a_i, vp_i = a_i, wp_i = a_i;
     if (live) {
         a_i = wk.a(slot, j)[i];
@@ -1272,9 +1306,9 @@ __global__ __launch_bounds__(kPBlock) void k_recur(Geom g, Work<R> wk, SrcList L
     double pv[kNvRecur] = {0.0, 0.0, 0.0, 0.0};
     if (live) {
         Z<R> r, q;
-        recur_update(a_i, b_i, v_i, w_i, vp_i, wp_i, al, alc, gj, bj, has_prev, r, q);
-        wk.f(slot, 2)[i] = r;
-        wk.f(slot, 3)[i] = q;
+        recur_update(a_i, b_i, sj.v(v_i), sj.w(w_i), sp.v(vp_i), sp.w(wp_i), al, alc, gj, bj, has_prev, r, q);
+        wk.v(slot, j + 1)[i] = r;
+        wk.w(slot, j + 1)[i] = q;
         const double rr = r.re, ri = r.im, qr = q.re, qi = q.im;
         pv[0] = qr * rr + qi * ri;
         pv[1] = qr * ri - qi * rr;
@@ -1386,6 +1420,7 @@ __device__ __forceinline__ bool blk_scalars(const Coef& coef, int j, const doubl
     if (writer) {
         coef.beta[j] = beta;
         coef.gamma[j] = gam;
+        coef.ib[j] = 1.0;   // this basis is stored normalised
         if (j == 1) coef.misc[0] = beta;
     }
     ib = 1.0 / beta;
@@ -1610,7 +1645,7 @@ __global__ __launch_bounds__(kAsmBlock) void k_assemble(Geom g, Work<R> wk, SrcL
             v[i] = fload_nt<R>(field_base(wk.v(slot, min(j + i, jlast))), g.ldv, p, (unsigned)s);
 #pragma unroll
         for (int i = 0; i < kAsmAhead; ++i)
-            if (j + i <= jlast) acc = acc + coef.c[j + i] * zcast<double>(v[i]);
+            if (j + i <= jlast) acc = acc + coef.c[j + i] * zcast<double>((R)coef.ib[j + i] * v[i]);
     }
     const double nx = coef.misc[0];
     tile[l][p] = ((overlap && p >= 6) ? -nx : nx) * acc;
@@ -1649,8 +1684,8 @@ __global__ __launch_bounds__(kPBlock) void k_bwd_ra(Geom g, Work<R> wk, SrcList 
     Z<R> vb_i = mk<R>(0, 0), wb_i = vb_i, vn_i = vb_i, wn_i = vb_i, vj_i = vb_i, wj_i = vb_i, vp_i = vb_i,
          wp_i = vb_i;
     if (live) {
-        vb_i = wk.f(slot, 4)[i];
-        wb_i = wk.f(slot, 5)[i];
+        vb_i = wk.f(slot, 2)[i];
+        wb_i = wk.f(slot, 3)[i];
         vn_i = wk.v(slot, j + 1)[i];
         wn_i = wk.w(slot, j + 1)[i];
         vj_i = wk.v(slot, j)[i];
@@ -1660,6 +1695,7 @@ __global__ __launch_bounds__(kPBlock) void k_bwd_ra(Geom g, Work<R> wk, SrcList 
             wp_i = wk.w(slot, j - 1)[i];
         }
     }
+    const BasisScale<R> sn(coef, j + 1), sj(coef, j), sp(coef, has_prev ? j - 1 : j);
     const double beta = coef.beta[j + 1];
     const ZD gam = coef.gamma[j + 1];
     const double bbar_n = coef.bbar_tot[j + 1];
@@ -1681,9 +1717,15 @@ __global__ __launch_bounds__(kPBlock) void k_bwd_ra(Geom g, Work<R> wk, SrcList 
     const Z<R> c4 = zcast<R>(beta * cj(ombar));                  // conj(omegabar) beta
     double pv[kNvRA] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (live) {
+        vn_i = sn.v(vn_i);
+        wn_i = sn.w(wn_i);
+        vj_i = sj.v(vj_i);
+        wj_i = sj.w(wj_i);
+        vp_i = sp.v(vp_i);
+        wp_i = sp.w(wp_i);
         const Z<R> r = c1 * vb_i + c2 * wn_i;
         const Z<R> q = c3 * wb_i + c4 * vn_i;
-        wk.f(slot, 6 + (j & 1))[i] = r;
+        wk.f(slot, 4 + (j & 1))[i] = r;
         wk.sb(slot, j)[i] = q;
         const ZD rd = zcast<double>(r), qd = zcast<double>(q);
         const ZD p1 = cjmul(zcast<double>(vj_i), rd);
@@ -1718,8 +1760,8 @@ void launch_bwd_ra(const Geom& g, const Work<R>& wk, const SrcList& L, Coef coef
 // The recorded scalars of reverse step j, read at the top of the kernel so that
 // their loads share a round trip with the hops' instead of following the block sum.
 struct BwdCoefs {
-    ZD abar_T, gbar_T, alpha, etac, gnc;
-    double bbar_T, bn;
+    ZD abar_T, gbar_T, alpha, etac, gnc, icg;
+    double bbar_T, bn, ib;
 };
 __device__ __forceinline__ BwdCoefs bwd_coefs(const Coef& coef, int j, bool carry) {
     BwdCoefs c;
@@ -1730,6 +1772,8 @@ __device__ __forceinline__ BwdCoefs bwd_coefs(const Coef& coef, int j, bool carr
     c.etac = coef.misc[0] * cj(coef.c[j]);
     c.gnc = carry ? cj(coef.gamma[j + 1]) : mk<double>(0, 0);
     c.bn = carry ? coef.beta[j + 1] : 0.0;
+    c.ib = coef.ib[j];
+    c.icg = coef.icg[j];
     return c;
 }
 
@@ -1748,8 +1792,8 @@ __device__ __forceinline__ void bwd_rb_load(const Geom& g, const Work<R>& wk, in
     const bool carry = j + 1 < k_used;
     const FieldBase rw = field_base(wk.w(slot, j)), rv = field_base(wk.v(slot, j)), ra = field_base(wk.a(slot, j)),
                     rb = field_base(wk.b(slot, j)), re = field_base(wk.f(slot, 1));
-    const FieldBase rr = field_base(wk.f(slot, 6 + (j & 1))), rs = field_base(wk.sb(slot, j));
-    const FieldBase rrn = field_base(wk.f(slot, 6 + ((j + 1) & 1))), rsn = field_base(carry ? wk.sb(slot, j + 1)
+    const FieldBase rr = field_base(wk.f(slot, 4 + (j & 1))), rs = field_base(wk.sb(slot, j));
+    const FieldBase rrn = field_base(wk.f(slot, 4 + ((j + 1) & 1))), rsn = field_base(carry ? wk.sb(slot, j + 1)
                                                                                           : wk.sb(slot, j));
     const unsigned i = (unsigned)s;
 #pragma unroll
@@ -1795,6 +1839,7 @@ __device__ __forceinline__ void bwd_rb_finish_pre(const Geom& g, double kappa, c
     const Z<R> etac = zcast<R>(cf.etac);
     const Z<R> gnc = zcast<R>(cf.gnc);
     const R bn = (R)cf.bn;
+    const BasisScale<R> sc{(R)cf.ib, zcast<R>(cf.icg)};
     double pv[kNvRB] = {0.0, 0.0, 0.0};
     if (s < g.V) {
         const R kap = (R)kappa;
@@ -1803,8 +1848,8 @@ __device__ __forceinline__ void bwd_rb_finish_pre(const Geom& g, double kappa, c
 #pragma unroll
         for (int sp = 0; sp < 4; ++sp) {
             const R sg = sp < 2 ? R(1) : R(-1);
-            const Z<R> w_s = in.w[sp];
-            const Z<R> v_s = in.v[sp];
+            const Z<R> w_s = sc.w(in.w[sp]);
+            const Z<R> v_s = sc.v(in.v[sp]);
             const Z<R> a_s = in.a[sp];
             const Z<R> b_s = in.b[sp];
             Z<R> vb = etac * in.e[sp] + ca * b_s;
@@ -1830,8 +1875,8 @@ __device__ __forceinline__ void bwd_rb_finish_pre(const Geom& g, double kappa, c
             d2r += x2.re;
             d2i += x2.im;
         }
-        store1_nt(wk.f(slot, 4), g.ldv, a, s, vbo);
-        store1_nt(wk.f(slot, 5), g.ldv, a, s, wbo);
+        store1_nt(wk.f(slot, 2), g.ldv, a, s, vbo);
+        store1_nt(wk.f(slot, 3), g.ldv, a, s, wbo);
         store1_nt(wk.ab(slot, j), g.ldv, a, s, abo);
         pv[0] = d1;
         pv[1] = d2r;
@@ -1845,8 +1890,8 @@ __device__ __forceinline__ void bwd_rb_finish(const Geom& g, double kappa, const
                                               int slot, int j, int k_used, int pslot, int a, int s,
                                               const double (&red)[kNvRA], const Z<R> (&accs)[4],
                                               const Z<R> (&accr)[4], const BwdCoefs& cf) {
-    const Z<R>* __restrict__ rbar_j = wk.f(slot, 6 + (j & 1));
-    const Z<R>* __restrict__ rbar_n = wk.f(slot, 6 + ((j + 1) & 1));
+    const Z<R>* __restrict__ rbar_j = wk.f(slot, 4 + (j & 1));
+    const Z<R>* __restrict__ rbar_n = wk.f(slot, 4 + ((j + 1) & 1));
     const Z<R>* __restrict__ sbar_j = wk.sb(slot, j);
     const bool carry = j + 1 < k_used;
     const Z<R>* __restrict__ sbar_n = carry ? wk.sb(slot, j + 1) : sbar_j;
@@ -1864,6 +1909,7 @@ __device__ __forceinline__ void bwd_rb_finish(const Geom& g, double kappa, const
     const Z<R> etac = zcast<R>(cf.etac);
     const Z<R> gnc = zcast<R>(cf.gnc);
     const R bn = (R)cf.bn;
+    const BasisScale<R> sc{(R)cf.ib, zcast<R>(cf.icg)};
     double pv[kNvRB] = {0.0, 0.0, 0.0};
     if (s < g.V) {
         const R kap = (R)kappa;
@@ -1877,8 +1923,8 @@ __device__ __forceinline__ void bwd_rb_finish(const Geom& g, double kappa, const
             const int pl = sp * 3 + a;
             const unsigned i = (unsigned)s;
             const R sg = sp < 2 ? R(1) : R(-1);
-            const Z<R> w_s = fload_nt<R>(rw, g.ldv, pl, i);
-            const Z<R> v_s = fload_nt<R>(rv, g.ldv, pl, i);
+            const Z<R> w_s = sc.w(fload_nt<R>(rw, g.ldv, pl, i));
+            const Z<R> v_s = sc.v(fload_nt<R>(rv, g.ldv, pl, i));
             const Z<R> a_s = fload_nt<R>(ra, g.ldv, pl, i);
             const Z<R> b_s = fload_nt<R>(rb, g.ldv, pl, i);
             Z<R> vb = etac * fload_nt<R>(re, g.ldv, pl, i) + ca * b_s;
@@ -1904,8 +1950,8 @@ __device__ __forceinline__ void bwd_rb_finish(const Geom& g, double kappa, const
             d2r += x2.re;
             d2i += x2.im;
         }
-        store1_nt(wk.f(slot, 4), g.ldv, a, s, vbo);
-        store1_nt(wk.f(slot, 5), g.ldv, a, s, wbo);
+        store1_nt(wk.f(slot, 2), g.ldv, a, s, vbo);
+        store1_nt(wk.f(slot, 3), g.ldv, a, s, wbo);
         store1_nt(wk.ab(slot, j), g.ldv, a, s, abo);
         pv[0] = d1;
         pv[1] = d2r;
@@ -1943,7 +1989,7 @@ void k_bwd_rb(const Z<RL>* __restrict__ U, Geom g, double kappa, double emu,
         gather_partials<kNvRA, BLK>(wk.p(slot, 1), npart_in, red);
         if (s < g.V) {
             const Z<R>* fs = wk.sb(slot, j);
-            const Z<R>* fr = wk.f(slot, 6 + (j & 1));
+            const Z<R>* fr = wk.f(slot, 4 + (j & 1));
             const Nbr n = neighbours(g, s);
             hop_all_pair<BLK>(accs, accr, U, fs, fr, g, s, a, n, (R)emu, (R)(1.0 / emu));
             mem_fence_compiler();
@@ -1977,7 +2023,7 @@ void k_bwd_rb_cg(const Z<RL>* __restrict__ U, Geom g, double kappa, double emu, 
         zero1(accr);
         if (s < g.V) {
             const Z<R>* fs = wk.sb(slot, j);
-            const Z<R>* fr = wk.f(slot, 6 + (j & 1));
+            const Z<R>* fr = wk.f(slot, 4 + (j & 1));
             const Nbr n = neighbours(g, s);
             if (wv == 1)
                 hop_two_dirs_pair_eager<0, 1>(accs, accr, U, fs, fr, g, s, a, n, (R)emu, (R)(1.0 / emu));
@@ -2030,7 +2076,7 @@ __global__ __launch_bounds__(kCBlock) void k_bwd_rb_ms(const Z<RL>* __restrict__
         if (e0 + q < L.n) live |= 1u << q;
         slot[q] = L.slot[e];
         fs[q] = wk.sb(slot[q], j);
-        fr[q] = wk.f(slot[q], 6 + (j & 1));
+        fr[q] = wk.f(slot[q], 4 + (j & 1));
         cf[q] = bwd_coefs(coef0.at(slot[q]), j, j + 1 < L.k[e]);
         gather_partials<kNvRA, kCBlock>(wk.p(slot[q], 1), npart_in, red[q]);
     }
@@ -2080,7 +2126,7 @@ __global__ __launch_bounds__(kDBlock, 2) void k_bwd_rb_dirs(const Z<RL>* __restr
         }
     };
     Z<R> accs[4], accr[4];
-    dir_pair(accs, accr, hops, U, (const Z<R>*)wk.sb(slot, j), (const Z<R>*)wk.f(slot, 6 + (j & 1)), g, min(s, g.V - 1),
+    dir_pair(accs, accr, hops, U, (const Z<R>*)wk.sb(slot, j), (const Z<R>*)wk.f(slot, 4 + (j & 1)), g, min(s, g.V - 1),
              w, (R)emu, (R)(1.0 / emu), sums);
     mem_fence_compiler();
     double red[kNvRA];
@@ -2126,12 +2172,27 @@ void launch_bwd_rb(const Z<RL>* U, const Geom& g, double kappa, double mu, const
 //   G_ab += -kappa sum_{s=0,1} [ e_f hP[s][a] conj(hQ[s][b]) + e_b hQ2[s][a] conj(hP2[s][b]) ]
 // with hP = P+(g5 p(x)), hQ = P+(q(x+nu)), hP2 = P-(g5 p(x+nu)), hQ2 = P-(q(x)) the
 // half spinors of the (1 +- g_nu) projectors, e_f = e^{+mu}, e_b = e^{-mu} for nu = t.
+// The basis scales go into the terms' factors; with float32 fields the vectors are formed
+// first, rounded as the other readers round them.
+template <typename R, typename F>
+__device__ __forceinline__ void scale_spinor(Spinor<R>& p, F f) {
+#pragma unroll
+    for (int sp = 0; sp < 4; ++sp)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            Z<R> t = f(p.c[sp][c]);
+            asm("" : "+v"(t.re), "+v"(t.im));   // rounded here: not contracted into the projection's sums
+            p.c[sp][c] = t;
+        }
+}
+
 template <int NU, typename R>
-__device__ void force_body(const Geom& g, double kappa, double emu, const Work<R>& wk, int slot, int k, int j0,
-                           int j1, int s, ZD* __restrict__ gout, int accumulate) {
+__device__ void force_body(const Geom& g, double kappa, double emu, const Work<R>& wk, const Coef& coef, int slot,
+                           int k, int j0, int j1, int s, ZD* __restrict__ gout, int accumulate) {
     const Nbr n = neighbours(g, s);
     const int y = n.fwd[NU];
     const double ef = (NU == 3) ? emu : 1.0, eb = (NU == 3) ? 1.0 / emu : 1.0;
+    constexpr bool narrow = sizeof(R) != sizeof(double);
     ZD G[3][3];
 #pragma unroll
     for (int a = 0; a < 3; ++a)
@@ -2139,17 +2200,33 @@ __device__ void force_body(const Geom& g, double kappa, double emu, const Work<R
         for (int b = 0; b < 3; ++b) G[a][b] = mk<double>(0, 0);
     for (int j = j0; j < j1; ++j) {
         Spinor<R> px, qx, py, qy;
+        const double ib = coef.ib[j];
         load_spinor(px, wk.ab(slot, j), g.ldv, s);
         load_spinor(qx, wk.v(slot, j), g.ldv, s);
         load_spinor(py, wk.ab(slot, j), g.ldv, y);
         load_spinor(qy, wk.v(slot, j), g.ldv, y);
-        force_pair<NU>(G, px, qx, py, qy, ef, eb);
+        if constexpr (narrow) {
+            const BasisScale<R> sc(coef, j);
+            scale_spinor(qx, [&](Z<R> r) { return sc.v(r); });
+            scale_spinor(qy, [&](Z<R> r) { return sc.v(r); });
+            force_pair<NU>(G, px, qx, py, qy, ef, eb);
+        } else {
+            force_pair<NU>(G, px, qx, py, qy, ef * ib, eb * ib);
+        }
         if (j < k) {
+            const ZD icg = coef.icg[j];
             load_spinor(px, wk.w(slot, j), g.ldv, s);
             load_spinor(qx, wk.sb(slot, j), g.ldv, s);
             load_spinor(py, wk.w(slot, j), g.ldv, y);
             load_spinor(qy, wk.sb(slot, j), g.ldv, y);
-            force_pair<NU>(G, px, qx, py, qy, ef, eb);
+            if constexpr (narrow) {
+                const BasisScale<R> sc(coef, j);
+                scale_spinor(px, [&](Z<R> t) { return sc.w(t); });
+                scale_spinor(py, [&](Z<R> t) { return sc.w(t); });
+                force_pair<NU>(G, px, qx, py, qy, ef, eb);
+            } else {
+                force_pair_scaled<NU>(G, px, qx, py, qy, ef * icg, eb * icg);
+            }
         }
     }
 #pragma unroll
@@ -2167,7 +2244,7 @@ __device__ void force_body(const Geom& g, double kappa, double emu, const Work<R
 // that neighbour spinors are mostly still in L2.
 template <typename R>
 __global__ __launch_bounds__(4 * kSites) void k_force(Geom g, double kappa, double emu, Work<R> wk, SrcList L,
-                                                      int nchunk, ZD* __restrict__ gpart, int jlo, int jhi,
+                                                      Coef coef0, int nchunk, ZD* __restrict__ gpart, int jlo, int jhi,
                                                       int accumulate) {
     const int nu = __builtin_amdgcn_readfirstlane(threadIdx.x / kSites);
     const int sb = g.sbmap ? g.sbmap[blockIdx.x] : (int)blockIdx.x;
@@ -2181,20 +2258,21 @@ __global__ __launch_bounds__(4 * kSites) void k_force(Geom g, double kappa, doub
     const int j0 = jlo + (int)((long long)n * chunk / nchunk);
     const int j1 = jlo + (int)((long long)n * (chunk + 1) / nchunk);
     ZD* out = gpart + ((size_t)slot * nchunk + chunk) * 36 * g.ldv;
+    const Coef coef = coef0.at(slot);
     switch (nu) {
-        case 0: force_body<0>(g, kappa, emu, wk, slot, k, j0, j1, s, out, accumulate); break;
-        case 1: force_body<1>(g, kappa, emu, wk, slot, k, j0, j1, s, out, accumulate); break;
-        case 2: force_body<2>(g, kappa, emu, wk, slot, k, j0, j1, s, out, accumulate); break;
-        default: force_body<3>(g, kappa, emu, wk, slot, k, j0, j1, s, out, accumulate); break;
+        case 0: force_body<0>(g, kappa, emu, wk, coef, slot, k, j0, j1, s, out, accumulate); break;
+        case 1: force_body<1>(g, kappa, emu, wk, coef, slot, k, j0, j1, s, out, accumulate); break;
+        case 2: force_body<2>(g, kappa, emu, wk, coef, slot, k, j0, j1, s, out, accumulate); break;
+        default: force_body<3>(g, kappa, emu, wk, coef, slot, k, j0, j1, s, out, accumulate); break;
     }
 }
 
 template <typename R>
-void launch_force(const Geom& g, double kappa, double mu, const Work<R>& wk, const SrcList& L, int nchunk, ZD* gpart,
-                  hipStream_t st, int jlo, int jhi, int accumulate) {
+void launch_force(const Geom& g, double kappa, double mu, const Work<R>& wk, const SrcList& L, Coef coef, int nchunk,
+                  ZD* gpart, hipStream_t st, int jlo, int jhi, int accumulate) {
     dim3 grid(g.sbmap ? g.nwg : np_stencil(g.V), nchunk, L.n);
-    hipLaunchKernelGGL(k_force<R>, grid, dim3(4 * kSites), 0, st, g, kappa, std::exp(mu), wk, L, nchunk, gpart, jlo,
-                       jhi, accumulate);
+    hipLaunchKernelGGL(k_force<R>, grid, dim3(4 * kSites), 0, st, g, kappa, std::exp(mu), wk, L, coef, nchunk, gpart,
+                       jlo, jhi, accumulate);
 }
 
 __device__ __forceinline__ double boundary_sign(const Geom& g, int nu, int s, int antiperiodic) {
@@ -2376,8 +2454,8 @@ int launch_ward(const Geom& g, const double* gsrc, const SrcList& L, const ZD* p
 template <typename R>
 __global__ __launch_bounds__(kBlock) void k_sgrad_dot(Geom g, Work<R> wk, SrcList L) {
     const int slot = L.slot[blockIdx.y];
-    const Z<R>* __restrict__ vbar = wk.f(slot, 4);
-    const Z<R>* __restrict__ wbar = wk.f(slot, 5);
+    const Z<R>* __restrict__ vbar = wk.f(slot, 2);
+    const Z<R>* __restrict__ wbar = wk.f(slot, 3);
     const Z<R>* __restrict__ x = wk.f(slot, 0);
     const int s = blockIdx.x * kBlock + threadIdx.x;
     double v[1] = {0.0};
@@ -2403,8 +2481,8 @@ __global__ __launch_bounds__(kBlock) void k_sgrad_out(Geom g, Work<R> wk, SrcLis
     const double c2 = (S / nx - red[0] / (nx * nx)) / nx;
     const int s = blockIdx.x * kBlock + threadIdx.x;
     if (s >= g.V) return;
-    const Z<R>* __restrict__ vbar = wk.f(slot, 4);
-    const Z<R>* __restrict__ wbar = wk.f(slot, 5);
+    const Z<R>* __restrict__ vbar = wk.f(slot, 2);
+    const Z<R>* __restrict__ wbar = wk.f(slot, 3);
     const Z<R>* __restrict__ x = wk.f(slot, 0);
     ZD* out = out_base + (size_t)L.src[e] * 12 * g.V;
 #pragma unroll
@@ -2437,11 +2515,12 @@ __global__ __launch_bounds__(kBlock) void k_biorth(Geom g, Work<R> wk, SrcList L
         const Z<R>* x = wk.f(slot, 0);
         const Z<R>* vk = wk.v(slot, ku);
         const Z<R>* wkk = wk.w(slot, ku);
+        const BasisScale<R> sc(coef0.at(slot), ku);
 #pragma unroll
         for (int p = 0; p < 12; ++p) {
             const ZD xs = zcast<double>(x[(size_t)p * g.ldv + s]);
-            const ZD xv = cjmul(xs, zcast<double>(vk[(size_t)p * g.ldv + s]));
-            const ZD wx = cjmul(zcast<double>(wkk[(size_t)p * g.ldv + s]), xs);
+            const ZD xv = cjmul(xs, zcast<double>(sc.v(vk[(size_t)p * g.ldv + s])));
+            const ZD wx = cjmul(zcast<double>(sc.w(wkk[(size_t)p * g.ldv + s])), xs);
             v[0] += xv.re;
             v[1] += xv.im;
             v[2] += wx.re;
@@ -2469,7 +2548,7 @@ int launch_biorth(const Geom& g, const Work<R>& wk, const SrcList& L, Coef coef,
     template void launch_assemble<R>(const Geom&, const Work<R>&, const SrcList&, Coef, const ZD*, int, ZD*,    \
                                      hipStream_t, int, int);                                                    \
     template void launch_bwd_ra<R>(const Geom&, const Work<R>&, const SrcList&, Coef, int, hipStream_t);        \
-    template void launch_force<R>(const Geom&, double, double, const Work<R>&, const SrcList&, int, ZD*,        \
+    template void launch_force<R>(const Geom&, double, double, const Work<R>&, const SrcList&, Coef, int, ZD*,  \
                                   hipStream_t, int, int, int);                                                  \
     template void launch_source_grad<R>(const Geom&, const Work<R>&, const SrcList&, Coef, ZD*, hipStream_t);   \
     template int launch_biorth<R>(const Geom&, const Work<R>&, const SrcList&, Coef, hipStream_t);

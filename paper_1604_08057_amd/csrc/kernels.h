@@ -37,13 +37,13 @@ int tmarch_chunks(const Geom& g, int* T, int maxn);
 // ---------------------------------------------------------------- batch workspace
 // Per-source lattice fields of a batch in the working precision.  Sources sit in
 // batch slots; every per-step array holds kcap fields per slot (step j at j - 1).
-constexpr int kNF = 8;   // per-slot fields: 0 psi, 1 eta, 2 r, 3 s, 4 vbar, 5 wbar, 6/7 rbar ring
+constexpr int kNF = 6;   // per-slot fields: 0 psi, 1 eta, 2 vbar, 3 wbar, 4/5 rbar ring
 constexpr int kNP = 4;   // per-slot partial-sum arrays
 
 template <typename R>
 struct Work {
-    Z<R>* V;    // v_j
-    Z<R>* W;    // w_j
+    Z<R>* V;    // r_j: v_j = r_j / beta_j
+    Z<R>* W;    // s_j: w_j = s_j / conj(gamma_j)
     Z<R>* A;    // a_j = H v_j
     Z<R>* B;    // b_j = H^dag w_j
     Z<R>* AB;   // abar_j (reverse pass)
@@ -135,7 +135,7 @@ void launch_bwd_rb(const Z<RL>* U, const Geom& g, double kappa, double mu, const
 // [jlo, min(jhi, k[e])] of each entry (jhi = 0: every step), stored, or added to
 // the partials already there (accumulate = 1).
 template <typename R>
-void launch_force(const Geom& g, double kappa, double mu, const Work<R>& wk, const SrcList& L, int nchunk, ZD* gpart,
+void launch_force(const Geom& g, double kappa, double mu, const Work<R>& wk, const SrcList& L, Coef coef, int nchunk, ZD* gpart,
                   hipStream_t st, int jlo = 1, int jhi = 0, int accumulate = 0);
 // dU[src] (canonical) from the chunk partials, boundary sign undone.
 void launch_force_reduce(const Geom& g, const ZD* gpart, int nchunk, const SrcList& L, int antiperiodic, ZD* dU,
