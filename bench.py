@@ -302,7 +302,7 @@ def stencil_large():
     b = ctx.kernel_bytes(KERNEL_APPLY)
     ctx.close()
     gbs = b / (ms / n * 1e-3) / 1e9
-    return {"lattice": "32^4", "kernel": "k_apply_tmarch<double, double>", "bytes_per_launch": b,
+    return {"lattice": "32^4", "kernel": "k_apply_dirs<double, double>", "bytes_per_launch": b,
             "mean_ms": ms / n, "achieved_GBs": gbs, "frac_of_peak": gbs / HBM_PEAK_GBS}
 
 

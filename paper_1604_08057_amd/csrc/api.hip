@@ -2752,7 +2752,7 @@ double tslov_kernel_bytes(const tslov_ctx* c, int which) {
     const double z = (double)c->zsize(), zl = (double)c->lsize();
     const double V = (double)c->g.V;
     switch (which) {
-        case 0: return V * (6 * 12 * z + 36 * zl);      // read r, s, links; write v, w, a, b
+        case 0: return V * (4 * 12 * z + 36 * zl);      // read r, s, links; write a, b
         case 1: return V * (12 * 12 * z + 36 * zl);     // read 9 fields and links; write 3 fields
         case 2: return V * (2 * 12 * sizeof(ZD) + 36 * zl);   // read in and links; write out (canonical)
         default: return 0.0;
