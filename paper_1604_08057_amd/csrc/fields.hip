@@ -838,10 +838,11 @@ struct BasisScale {
 
 // Epilogue of step j for one entry, after the hops: breakdown decisions from the
 // block-summed previous (omega, |r|^2, |s|^2) in `red`, the coefficient records,
-// the stores of v_j, w_j, a_j, b_j and the step's partial sums.  Every branch
+// the stores of a_j, b_j (at the first step also of the source, as both residuals) and the
+// step's partial sums.  Every branch
 // depends on block-uniform values only, so a block takes it as a whole.
 // replay: the step's coefficients are the recorded beta_j, gamma_j, and nothing but
-// the four fields is written (a runtime flag, so that a replayed step runs the
+// the fields is written (a runtime flag, so that a replayed step runs the
 // very instructions of the original one).
 template <typename R, int BLK>
 __device__ __forceinline__ void fwd_pair_finish(const Geom& g, double kappa, const Work<R>& wk, const Coef& coef,
