@@ -342,7 +342,10 @@ constexpr int kDBlock = 4 * kSites;
 // direction split: 12^4 (324 site blocks) 18.8, 24.2 -> 16.7, 22.0; 16^4 (1024) 45.0, 58.4 ->
 // 41.2, 50.2, with float32 links 40.8, 58.4 -> 31, 54; 16^3 x 32 (2048) 85, 135 -> 78, 124;
 // 8 entries of 10^4 (1256) 37.4, 48.0 -> 35.0, 44.7; but 14^4 (601) 26.6, 34.2 -> 27.9, 37.2
-// and 6 entries of 18^3 x 6 (3282) 78.8, 111 -> 80.9, 115.  float32 fields: no gain.
+// and 6 entries of 18^3 x 6 (3282) 78.8, 111 -> 80.9, 115.  float32 fields: no gain.  With
+// float32 links the reverse pair of the colour split needs 176 registers, two wavefronts per
+// SIMD, so there the direction split always serves it (14^4 46.4 -> 41.1 us, 24^4 534 -> 473,
+// 32^3 x 16 1048 -> 957; derivatives of 6 entries of 18^3 x 6 62.3 -> 59.8 ms).
 inline bool direction_split(const Geom& g, int n) {
     const long long b = (long long)np_stencil(g.V) * n, slots = 512, rounds = (b + slots - 1) / slots;
     if (n > 1 && rounds > 4) return false;
@@ -2158,7 +2161,7 @@ void launch_bwd_rb(const Z<RL>* U, const Geom& g, double kappa, double mu, const
                      coef, j, np);
     else {
         if constexpr (sizeof(R) == sizeof(double))
-            if (direction_split(g, L.n)) {
+            if (sizeof(RL) < sizeof(R) || direction_split(g, L.n)) {
                 timed_launch(k_bwd_rb_dirs<R, RL>, dim3(g.nwg, L.n), dim3(kDBlock), st, t, U, g, kappa, emu, wk, L, coef,
                              j, np);
                 return;

@@ -3,7 +3,8 @@
 Three sources of uneven Krylov size on lattices whose site blocks go out in one round of
 workgroups, so that a launch with one entry per workgroup takes the direction split; two
 entries per workgroup (forced) take the colour split.  Whole and ragged last site blocks,
-odd extents, float64 and float32 links, stored and regenerated Krylov vectors.  Both add the
+odd extents, a lattice whose last steps (one source left) take the colour split, but for the
+reverse pair with float32 links, float64 and float32 links, stored and regenerated Krylov vectors.  Both add the
 same products in the same order, so every output is compared bit for bit, but for the
 link gradient of the regenerated run, whose sum over 15 steps is cut elsewhere (1e-13).
 """
@@ -18,7 +19,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32links"])
-@pytest.mark.parametrize("dims", [(9, 10, 10, 10), (8, 8, 8, 17), (13, 11, 7, 9)])
+@pytest.mark.parametrize("dims", [(9, 10, 10, 10), (8, 8, 8, 17), (13, 11, 7, 9), (14, 14, 14, 14)])
 def test_direction_split_bits(dims, precision):
     from paper_1604_08057_amd import Context
     r = np.random.default_rng(sum(dims))
