@@ -41,7 +41,17 @@ struct __align__(16) Row {
 __device__ __forceinline__ double swap_pair(double v) { return dpp_d<kDppSwap1>(v); }
 __device__ __forceinline__ ZD swap_pair(ZD v) { return mk<double>(swap_pair(v.re), swap_pair(v.im)); }
 
-// p(z)/p'(z) of p = det(z - T) on rows lo .. lo + n - 1 by a pair of lanes.  Side 0 walks
+// a b with the bits of b a: a fused product would round the exchanged operands differently.
+__device__ __forceinline__ ZD mul_symmetric(ZD a, ZD b) {
+#pragma clang fp contract(off)
+    const double re = a.re * b.re - a.im * b.im, im = a.re * b.im + a.im * b.re;
+    return mk<double>(re, im);
+}
+
+// p(z)/p'(z) of p = det(z - T) on rows lo .. lo + n - 1 by a pair of lanes, the same bits in
+// both: what joins the sides (rq, ends and s1 + s1' below) is symmetric in them to the last
+// bit, so zi, prev and done agree too, and no lane settles alone and leaves its partner half
+// a matrix (near a root D is all cancellation).  Side 0 walks
 // the leading minors P_1 .. P_h down from the first row, side 1 the trailing minors Q up from
 // the last one, each by the ratios of successive minors and their logarithmic derivatives
 // (ritz.cpp newton_batch); they meet in p = P_h Q - w P_{h-1} Q', w the coupling of rows
@@ -80,7 +90,7 @@ __device__ __forceinline__ ZD newton_correction(const Row* __restrict__ T, int l
     }
     const ZD r = mk<double>(rr, ri), s1 = mk<double>(sr, si), s0 = mk<double>(pr, pi);
     const ZD w = h > 0 ? mk<double>(T[lo + h].wr, T[lo + h].wi) : mk<double>(0, 0);
-    const ZD rq = r * swap_pair(r), D = rq - w, ends = s0 + swap_pair(s0);
+    const ZD rq = mul_symmetric(r, swap_pair(r)), D = rq - w, ends = s0 + swap_pair(s0);
     const ZD den = D * ends + rq * (s1 + swap_pair(s1) - ends);
     return D * mk<double>(den.re * rcp2(norm2(den)), -den.im * rcp2(norm2(den)));
 }
@@ -259,14 +269,14 @@ __global__ __launch_bounds__(kGroupThreads) void k_ritz(Coef coef, int k, int nd
             zi = start_point(z, l0, m, i);
         }
         __syncthreads();
-        if (mine) z[i] = zi;
+        if (mine && side == 0) z[i] = zi;
         __syncthreads();
         bool done = !mine;
         double prev = INFINITY;
         for (sweeps = 1; sweeps <= kMaxSweeps; ++sweeps) {
             if (!done) done = root_step(T, z, l0, m, i, side, nd == 0 && d == 0, zi, prev);
             const int open = __syncthreads_or(!done);   // every sum has read the old roots
-            if (mine) z[i] = zi;
+            if (mine && side == 0) z[i] = zi;
             __syncthreads();
             if (!open) break;
         }
