@@ -9,10 +9,10 @@
 // N = 2, 4, 8, ... by inverting full matrices; the partial fractions give one large member
 // from N - 1 independent tridiagonal solves, one per thread:
 //     c = T e_1/(s N) + sum_m W_m x_m,   (T - i s t_m) x_m = e_1,   t_m = tan phi_m.
-// The even m are the member N/2 and the odd m its midpoint twin tanh(N/2 artanh x), whose
-// errors are opposite to first order: half their difference squares into the error of their
-// mean, so it is the estimate by which the host accepts the result or refuses it (then a
-// larger N, then Newton).
+// The even m are the member N/2 and the odd m its midpoint twin tanh(N/2 arcoth x).  Half
+// their difference is 1/sinh(N h), h = arcoth x, of which exp(-N h) is left in their mean, so
+// the difference bounds the result's error; the host accepts the result by it, at rounding
+// level, or refuses it (then a larger N, then Newton).
 // Bound: the chain of 2 k dependent complex steps of each thread, whatever N up to the
 // chip's width: 49 us at k = 200, 94 us at k = 400 (both sweeps), in place of 1.3 ms and
 // 4.5 ms of Gauss-Jordan sweeps and products.
@@ -67,11 +67,10 @@ __device__ __forceinline__ double rat_scale(const Coef& coef, int k) {
 
 // Both sweeps of the tridiagonal solves, thread = pole n (m = n - (N/2 - 1)), no pivoting:
 // from the last row up  d_j = alpha_j - t - beta_{j+1} gamma_{j+1} / d_{j+1},  then down
-// x_1 = 1 / d_1, x_j = -beta_j x_{j-1} / d_j.  A small d_j at one pole perturbs that pole's
-// term by its reciprocal and the sum by 1/N of it (on Krylov matrices up to k = 400 the
-// smallest |d_j| over all poles is 4e-4, and c agrees with the Schur form to its accuracy,
-// 1e-14).  Row j of the entry's plane (ld poles): 1/d_j after the first sweep, W x_j after
-// the second.
+// x_1 = 1 / d_1, x_j = -beta_j x_{j-1} / d_j.  A small d_j does no harm: every d_j is that of
+// a row whose alpha_j - t and beta gamma are changed by a few ulps, and the x_j are products
+// (pivots of 1e-15 planted at a pole leave c good to 1e-15).  Row j of the entry's plane (ld
+// poles): 1/d_j after the first sweep, W x_j after the second.
 __global__ __launch_bounds__(kRT) void k_rat_sweeps(Coef coef0, SrcList L, RatWork w, int N) {
     extern __shared__ ZD rs[];   // alpha_j, beta_j gamma_j and beta_j (index j - 1)
     const int e = blockIdx.y, k = L.k[e];
