@@ -138,7 +138,10 @@ tslov_status tslov_apply_h(tslov_ctx* ctx, const void* in, void* out, int dagger
  * 16^4; float32: twice that), else ERR_ARG.  It never times launches and never picks
  * the marching chunk length by timing (it uses the context's pick if one was made,
  * else the built-in choice).  It uses no workspace: calls of different contexts,
- * streams or threads do not disturb each other. */
+ * streams or threads do not disturb each other.  (Where in and out share bytes the
+ * operator reads a copy of the input: tslov_apply_dw and tslov_apply_h keep it in the
+ * context's workspace, this call in a static array of 32 MiB per device, on which
+ * such calls race unless the caller serialises them.) */
 tslov_status tslov_apply_h_noalloc(tslov_ctx* ctx, const void* in, void* out, int dagger);
 
 /* Optional deflation by known eigenpairs of H (Sec. 3: the standard projection

@@ -10,8 +10,8 @@
 #include <algorithm>
 #include <atomic>
 #include <chrono>
-#include <mutex>
 #include <cmath>
+#include <cstdint>
 #include <cstring>
 #include <numeric>
 #include <string>
@@ -119,6 +119,11 @@ std::vector<int> site_block_order(const Geom& g, int& nwg) {
 // takes a lattice.
 constexpr size_t kNoAllocBytes = (size_t)32 << 20;
 
+// Copy of that entry point's input where the caller's arrays overlap: one canonical spinor
+// (float64 complex in every precision) of any lattice it takes.  Each device holds its own
+// while the process lives; host code reaches it only through hipGetSymbolAddress.
+static __device__ __align__(256) char noalloc_input[kNoAllocBytes];
+
 // A captured launch sequence and the key (list, sizes, buffers, launch shapes) it
 // was captured for.
 struct LoopGraph {
@@ -138,6 +143,7 @@ struct tslov_ctx {
     hipStream_t st = nullptr;
     hipStream_t side = nullptr;   // the sign calls' Ritz values, beside the projected-matrix step
     int device = 0;
+    void* noalloc_in = nullptr;   // this device's noalloc_input
     size_t lds_max = 65536;
     int links_set = 0;
     int diag = 0;    // tslov_set_diagnostics flags
@@ -150,6 +156,7 @@ struct tslov_ctx {
     Buf U64, U32;
     Buf badflag;     // device int: a non-finite link element was seen
     Buf sbmap;       // Geom::sbmap
+    Buf opin;        // copy of the operator's input where the caller's arrays overlap
     // batch workspace: per slot, kcap steps of v, w, a = Hv, b = H^dag w (and
     // abar, sbar for the derivative), kNF fields and kNP partial arrays
     Buf basisV, basisW, basisA, basisB, abarS, sbarS;
@@ -2089,8 +2096,11 @@ tslov_status tslov_create(const tslov_lattice_desc* d, void* stream, tslov_ctx**
     HIPCHK(hipGetDevice(&dev));
     hipDeviceProp_t prop;
     HIPCHK(hipGetDeviceProperties(&prop, dev));
+    void* noalloc_in = nullptr;
+    HIPCHK(hipGetSymbolAddress(&noalloc_in, HIP_SYMBOL(noalloc_input)));
     tslov_ctx* c = new tslov_ctx();
     c->device = dev;
+    c->noalloc_in = noalloc_in;
     c->lds_max = prop.sharedMemPerBlock ? prop.sharedMemPerBlock : 65536;
     c->g.nx = d->dims[0];
     c->g.ny = d->dims[1];
@@ -2126,7 +2136,7 @@ tslov_status tslov_create(const tslov_lattice_desc* d, void* stream, tslov_ctx**
 void tslov_destroy(tslov_ctx* c) {
     if (!c) return;
     (void)hipStreamSynchronize(c->st);
-    for (Buf* b : {&c->trial, &c->solvebuf, &c->physbuf, &c->U64, &c->U32, &c->badflag, &c->nestbuf, &c->blk, &c->bdefl, &c->deflb, &c->curdefl, &c->sbmap, &c->basisV, &c->basisW, &c->basisA, &c->basisB, &c->abarS, &c->sbarS,
+    for (Buf* b : {&c->trial, &c->solvebuf, &c->physbuf, &c->U64, &c->U32, &c->badflag, &c->nestbuf, &c->blk, &c->bdefl, &c->deflb, &c->curdefl, &c->sbmap, &c->opin, &c->basisV, &c->basisW, &c->basisA, &c->basisB, &c->abarS, &c->sbarS,
                    &c->fields, &c->part, &c->coefmem, &c->dense, &c->rat, &c->ritz, &c->denseInt, &c->densePart, &c->denseDelta,
                    &c->gpart, &c->gsrc, &c->bout, &c->wardp, &c->canon, &c->deflw, &c->deflx, &c->cgf, &c->cgp,
                    &c->cgs, &c->ckpt})
@@ -2168,6 +2178,16 @@ static tslov_status apply_op(tslov_ctx* c, const void* in, void* out, double mu,
         return fail(TSLOV_ERR_ARG, "lattice too large for the allocation-free operator (" +
                                        std::to_string(2 * c->field_bytes()) + " bytes of fields, at most " +
                                        std::to_string(kNoAllocBytes) + ")");
+    // The kernel reads neighbours from `in` while other blocks write `out`: arrays that share
+    // bytes need a copy of the input.
+    const size_t bytes = (size_t)12 * c->g.V * sizeof(ZD);
+    const uintptr_t a = (uintptr_t)in, b = (uintptr_t)out;
+    if ((a < b ? b - a : a - b) < bytes) {
+        if (!no_alloc) CHK(ensure(c->opin, bytes));
+        void* copy = no_alloc ? c->noalloc_in : c->opin.p;
+        HIPCHK(hipMemcpyAsync(copy, in, bytes, hipMemcpyDeviceToDevice, c->st));
+        in = copy;
+    }
     switch (c->precision) {
         case TSLOV_MIXED: CHK((apply_fields<float, float>(c, in, out, mu, g5in, g5out, no_alloc))); break;
         case TSLOV_FP32_LINKS: CHK((apply_fields<double, float>(c, in, out, mu, g5in, g5out, no_alloc))); break;

@@ -237,8 +237,7 @@ class Context:
         return out
 
     def apply_h_noalloc(self, x: torch.Tensor, out: torch.Tensor, dagger: bool = False) -> torch.Tensor:
-        """apply_h with no device allocation in the library (staging in its static
-        per-device array); the caller provides out."""
+        """apply_h with no device allocation in the library; the caller provides out."""
         x = self._spinor(x, "x")
         out = self._spinor(out, "out")
         _check(self.lib, self.lib.tslov_apply_h_noalloc(self.handle, _ptr(x), _ptr(out), int(dagger)))
