@@ -162,8 +162,7 @@ struct tslov_ctx {
     Buf basisV, basisW, basisA, basisB, abarS, sbarS;
     Buf fields, part, coefmem;
     Buf dense, denseInt, densePart, denseDelta;
-    Buf rat;         // rational sign step: pole plane, row partials, estimate
-    Buf ritz;        // device Ritz summary (three doubles)
+    Buf ritz;        // device Ritz summary: the result, the matrix, both sets of roots, their state
     Buf gpart, gsrc;
     Buf bout;        // per-entry canonical y and dpsi (Ward check)
     Buf wardp;       // Ward block maxima
@@ -506,7 +505,7 @@ size_t bytes_per_source(const tslov_ctx* c, int kcap, int grad, int m = 0) {
 size_t held_bytes(const tslov_ctx* c) {
     size_t t = 0;
     for (const Buf* b : {&c->basisV, &c->basisW, &c->basisA, &c->basisB, &c->abarS, &c->sbarS, &c->fields, &c->part,
-                         &c->dense, &c->rat, &c->gpart, &c->bout, &c->ckpt})
+                         &c->dense, &c->gpart, &c->bout, &c->ckpt})
         t += b->n;
     return t;
 }
@@ -917,14 +916,15 @@ constexpr int kRatPoles[2] = {1024, 8192};
 constexpr double kRatAccept = 2.220446049250313e-16;
 
 // c = sgn(T) e_1 of one entry by the rational step; *done = 0 where its estimate refuses it.
+// The pole plane lies in the Newton iteration's matrices, which wait for its answer.
 tslov_status rational_step(tslov_ctx* c, const SrcList& L, int N, int* done) {
     tslov::RatWork w;
     w.ld = N;
     w.kcap = L.k[0];
     const size_t n = (size_t)w.kcap * w.ld;
-    CHK(ensure(c->rat, n * sizeof(ZD) + (size_t)(2 * w.kcap + 2) * sizeof(double)));
+    CHK(ensure(c->dense, n * sizeof(ZD) + (size_t)(2 * w.kcap + 2) * sizeof(double)));
     CHK(ensure_host_part(c, 2));
-    w.mem = c->rat.as<ZD>();
+    w.mem = c->dense.as<ZD>();
     w.rows = (double*)(w.mem + n);
     w.acc = w.rows + (size_t)2 * w.kcap;
     tslov::launch_ratsign(c->coef, L, w, N, c->st);
@@ -950,7 +950,9 @@ tslov_status dense_step(tslov_ctx* c, const SrcList& L, int grad, std::vector<in
         if (stagnated) stagnated->assign(1, 0);
         for (int N : kRatPoles) {
             int done = 0;
-            CHK(rational_step(c, L, N, &done));
+            const tslov_status st = rational_step(c, L, N, &done);
+            if (st == TSLOV_ERR_OOM) break;   // the Newton iteration may need less
+            CHK(st);
             ++iters[0];
             if (done) return TSLOV_OK;
         }
@@ -2137,7 +2139,7 @@ void tslov_destroy(tslov_ctx* c) {
     if (!c) return;
     (void)hipStreamSynchronize(c->st);
     for (Buf* b : {&c->trial, &c->solvebuf, &c->physbuf, &c->U64, &c->U32, &c->badflag, &c->nestbuf, &c->blk, &c->bdefl, &c->deflb, &c->curdefl, &c->sbmap, &c->opin, &c->basisV, &c->basisW, &c->basisA, &c->basisB, &c->abarS, &c->sbarS,
-                   &c->fields, &c->part, &c->coefmem, &c->dense, &c->rat, &c->ritz, &c->denseInt, &c->densePart, &c->denseDelta,
+                   &c->fields, &c->part, &c->coefmem, &c->dense, &c->ritz, &c->denseInt, &c->densePart, &c->denseDelta,
                    &c->gpart, &c->gsrc, &c->bout, &c->wardp, &c->canon, &c->deflw, &c->deflx, &c->cgf, &c->cgp,
                    &c->cgs, &c->ckpt})
         release(*b);
