@@ -476,7 +476,6 @@ const Z<RL>* links(const tslov_ctx* c) {
     else return c->U32.as<Z<RL>>();
 }
 
-// Device bytes one source of up to kcap steps needs (workspace sizing).
 // Chunks of steps the force contraction splits each entry into (its partials are
 // summed afterwards): about 2^18 threads in all, and at least 16 chunks so that a
 // large lattice does not leave each thread a loop over every step.  A segment of m
@@ -490,6 +489,7 @@ int force_chunks(int V, int m) {
     return m > 0 ? std::min(whole, std::max({fill, (m + 4) / 5, 1})) : whole;
 }
 
+// Device bytes one source of up to kcap steps needs (workspace sizing).
 size_t bytes_per_source(const tslov_ctx* c, int kcap, int grad, int m = 0) {
     const size_t fb = c->field_bytes();
     const int ring = ring_steps(kcap, m);
@@ -498,7 +498,7 @@ size_t bytes_per_source(const tslov_ctx* c, int kcap, int grad, int m = 0) {
     b += (size_t)tslov::kNP * c->pstride() * sizeof(double) + coef_bytes(1, kcap);
     b += (size_t)6 * kcap * kcap * sizeof(ZD) + (size_t)tslov::dense_pstride(kcap) * sizeof(double);
     if (grad)
-        b += (size_t)(force_chunks(c->g.V, m) + 1) * 36 * c->g.ldv * sizeof(ZD) + (size_t)2 * 12 * c->g.V * sizeof(ZD);
+        b += (size_t)(force_chunks(c->g.V, ring ? m : 0) + 1) * 36 * c->g.ldv * sizeof(ZD) + (size_t)2 * 12 * c->g.V * sizeof(ZD);
     return b;
 }
 
@@ -918,31 +918,33 @@ constexpr double kRatAccept = 2.220446049250313e-16;
 // c = sgn(T) e_1 of one entry by the rational step; *done = 0 where its estimate refuses it.
 // The pole plane lies in the Newton iteration's matrices, which wait for its answer.
 tslov_status rational_step(tslov_ctx* c, const SrcList& L, int N, int* done) {
-    tslov::RatWork w;
-    w.ld = N;
-    w.kcap = L.k[0];
-    const size_t n = (size_t)w.kcap * w.ld;
-    CHK(ensure(c->dense, n * sizeof(ZD) + (size_t)(2 * w.kcap + 2) * sizeof(double)));
+    const int k = L.k[0];
+    const size_t n = (size_t)k * N;
+    CHK(ensure(c->dense, n * sizeof(ZD) + (size_t)(2 * k + 2) * sizeof(double)));
     CHK(ensure_host_part(c, 2));
-    w.mem = c->dense.as<ZD>();
-    w.rows = (double*)(w.mem + n);
-    w.acc = w.rows + (size_t)2 * w.kcap;
-    tslov::launch_ratsign(c->coef, L, w, N, c->st);
+    tslov::RatWork w;
+    w.buf = c->dense.as<ZD>();
+    w.rows = (double*)(w.buf + n);
+    w.acc = w.rows + (size_t)2 * k;
+    w.ld = N;
+    tslov::launch_ratsign(c->coef.at(L.slot[0]), k, w, N, c->st);
     HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(c->host_part, w.acc, 2 * sizeof(double), hipMemcpyDeviceToHost, c->st));
     HIPCHK(hipStreamSynchronize(c->st));
     const double* a = c->host_part;
-    const double tol = kRatAccept * std::max(L.k[0], 16);
+    const double tol = kRatAccept * std::max(k, 16);
     *done = a[0] <= tol * tol * a[1] && std::isfinite(a[1]);
     return TSLOV_OK;
 }
 
 // sgn(T) (and the Frechet step) of every entry, coefficients c_j and adjoint seeds.  The
 // sign alone comes from the rational step, or from the Newton iteration where that does
-// not settle; iters: the pole sets taken, or the Newton iterations.  The derivative keeps
-// the Newton iteration: the reverse recursion amplifies the last bits of its seeds (two
-// equally accurate steps, 1e-14 apart, moved dS/dU by up to 1e-7 at 6x18^3, mu = 0.5), so
-// only one of the two routes gives reproducible derivatives.
+// not settle; iters: the pole sets taken, or the Newton iterations.  The block process takes
+// it too: its derivative is V c, with c as good as the sign's (and not worse than Newton's on
+// its matrices, see kRatAccept).  The derivative by the reverse recursion keeps the Newton
+// iteration: that recursion amplifies the last bits of its seeds (two equally accurate
+// steps, 1e-14 apart, moved dS/dU by up to 1e-7 at 6x18^3, mu = 0.5), so only one of the
+// two routes gives reproducible derivatives.
 tslov_status dense_step(tslov_ctx* c, const SrcList& L, int grad, std::vector<int>& iters,
                         std::vector<int>* stagnated = nullptr) {
     if (!grad && L.n == 1) {
@@ -1742,8 +1744,7 @@ tslov_status pick_apply_chunk(tslov_ctx* c, const Z<RL>* U, const ZD* a, ZD* b, 
         for (int i = 0; i < n; ++i) {
             const size_t x = (size_t)2 * (r * n + i);
             (void)hipEventRecord(ev[x], c->st);
-            tslov::launch_apply<R, RL>(U, a, b, c->g, c->kappa, mu, g5in, g5out, c->st, tslov::Timing{},
-                                                 cand[i]);
+            tslov::launch_apply<R, RL>(U, a, b, c->g, c->kappa, mu, g5in, g5out, c->st, tslov::Timing{}, cand[i]);
             (void)hipEventRecord(ev[x + 1], c->st);
         }
     const hipError_t es = hipEventSynchronize(ev.back());
@@ -1774,8 +1775,8 @@ tslov_status apply_fields(tslov_ctx* c, const void* in, void* out, double mu, in
     if (!c->tm_T_forced && !no_alloc)
         CHK((pick_apply_chunk<R, RL>(c, U, (const ZD*)in, (ZD*)out, mu, g5in, g5out)));
     tslov::launch_apply<R, RL>(U, (const ZD*)in, (ZD*)out, c->g, c->kappa, mu, g5in, g5out, c->st,
-                                         no_alloc ? tslov::Timing{} : TimedLaunch(c, 2).t,
-                                         c->tm_T_forced ? c->tm_T_forced : std::max(c->tm_T, 0));
+                               no_alloc ? tslov::Timing{} : TimedLaunch(c, 2).t,
+                               c->tm_T_forced ? c->tm_T_forced : std::max(c->tm_T, 0));
     return TSLOV_OK;
 }
 

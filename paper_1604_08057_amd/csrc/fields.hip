@@ -129,50 +129,11 @@ __device__ __forceinline__ void zero1(Z<R> (&p)[4]) {
     for (int sp = 0; sp < 4; ++sp) p[sp] = mk<R>(0, 0);
 }
 
-// Both hops of direction NU for two fields sharing the link rows: field A at +mu,
-// field B at -mu (the temporal factors swap).
-template <int NU, typename R, typename RL>
-__device__ __forceinline__ void hop_dir_pair1(Z<R> (&acca)[4], Z<R> (&accb)[4], const Z<RL>* __restrict__ U,
-                                              const Z<R>* __restrict__ fa, const Z<R>* __restrict__ fb,
-                                              const Geom& g, int s, int a, const Nbr& n, R ep, R em) {
-    const R up = (NU == 3) ? ep : R(1), dn = (NU == 3) ? em : R(1);
-    Z<R> u[3];
-    Spinor<R> p;
-    load_row(u, U, g.ldv, NU, a, s);
-    load_spinor(p, fa, g.ldv, n.fwd[NU]);
-    hop1<NU, +1>(acca, u, p, up);
-    load_spinor(p, fb, g.ldv, n.fwd[NU]);
-    hop1<NU, +1>(accb, u, p, dn);
-    load_col_conj(u, U, g.ldv, NU, a, n.bwd[NU]);
-    load_spinor(p, fa, g.ldv, n.bwd[NU]);
-    hop1<NU, -1>(acca, u, p, dn);
-    load_spinor(p, fb, g.ldv, n.bwd[NU]);
-    hop1<NU, -1>(accb, u, p, up);
-}
-
-// All eight hops of two fields (colour a) sharing the link rows (A at +mu, B at
-// -mu), a rolled loop over a wavefront-uniform switch: the colour split, with
-// several wavefronts per SIMD, so one operand's loads in flight at a time and few
-// registers.  (The colour grid's pair kernels use hop_two_dirs_pair_eager.)
-template <int BLK, typename R, typename RL>
-__device__ __forceinline__ void hop_all_pair(Z<R> (&acca)[4], Z<R> (&accb)[4], const Z<RL>* __restrict__ U,
-                                             const Z<R>* __restrict__ fa, const Z<R>* __restrict__ fb,
-                                             const Geom& g, int s, int a, const Nbr& n, R ep, R em) {
-#pragma unroll 1
-    for (int nu = 0; nu < 4; ++nu) {
-        switch (nu) {
-            case 0: hop_dir_pair1<0>(acca, accb, U, fa, fb, g, s, a, n, ep, em); break;
-            case 1: hop_dir_pair1<1>(acca, accb, U, fa, fb, g, s, a, n, ep, em); break;
-            case 2: hop_dir_pair1<2>(acca, accb, U, fa, fb, g, s, a, n, ep, em); break;
-            default: hop_dir_pair1<3>(acca, accb, U, fa, fb, g, s, a, n, ep, em); break;
-        }
-    }
-}
-
-// Two directions at once for two fields sharing the link rows: all sixteen
-// operands (four link rows, eight neighbour spinors) issued before any arithmetic,
-// one memory round trip for both directions.  Needs more than 256 registers: for
-// kernels whose grid leaves one wavefront per SIMD anyway (the colour grid).
+// Two directions at once for two fields sharing the link rows (field A at +mu, field B at
+// -mu: the temporal factors swap): all sixteen operands (four link rows, eight neighbour
+// spinors) issued before any arithmetic, one memory round trip for both directions.
+// Needs more than 256 registers: for kernels whose grid leaves one wavefront per SIMD
+// anyway (the colour grid).
 template <int NU0, int NU1, typename R, typename RL>
 __device__ __forceinline__ void hop_two_dirs_pair_eager(Z<R> (&acca)[4], Z<R> (&accb)[4], const Z<RL>* __restrict__ U,
                                                         const Z<R>* __restrict__ fa, const Z<R>* __restrict__ fb,
@@ -750,8 +711,8 @@ __global__ __launch_bounds__(kDirBlock) void k_apply_dirs(const Z<RL>* __restric
 
 // The march takes lattices whose (x, y, z) tiles split evenly over the XCDs.
 template <typename R, typename RL>
-void launch_apply(const Z<RL>* U, const ZD* in, ZD* out, const Geom& g, double kappa, double mu, int g5_in,
-                            int g5_out, hipStream_t st, Timing t, int tm_T) {
+void launch_apply(const Z<RL>* U, const ZD* in, ZD* out, const Geom& g, double kappa, double mu, int g5_in, int g5_out,
+                  hipStream_t st, Timing t, int tm_T) {
     const R ep = (R)std::exp(mu), em = (R)std::exp(-mu);
     auto go = [&](auto kernel, int nb, int T) {
         timed_launch(kernel, dim3(nb), dim3(kDirBlock), st, t, U, in, out, g, (R)kappa, ep, em, g5_in, g5_out, T);
@@ -1964,18 +1925,10 @@ __device__ __forceinline__ void bwd_rb_finish(const Geom& g, double kappa, const
     write_partials_at<kNvRB, BLK>(wk.p(slot, 0), pslot, pv);
 }
 
-// Reverse step j (one entry per workgroup, grid.y = entry):
-//   vbar_j = |x| conj(c_j) eta + H^dag rbar_j + alphabar_j b_j - conj(alpha_j) rbar_j - conj(gamma_{j+1}) rbar_{j+1},
-//   wbar_j = H sbar_j + conj(alphabar_j) a_j - alpha_j sbar_j - beta_{j+1} sbar_{j+1},
-// using the forward pass's a_j and b_j = H^dag w_j, so the stencil acts on rbar_j
-// (at -mu) and sbar_j (at +mu) only.  Stores abar_j for the force and emits
-// partials of Re vbar_j^H v_j and wbar_j^H w_j.  The last step (j = k_used) has
-// no residual adjoints: abar = alphabar w, vbar = |x| conj(c) eta + alphabar b,
-// wbar = conj(alphabar) a.
-template <typename R, bool LAST, int BLK, typename RL>
+// The last reverse step (j = k_used), which has no residual adjoints and so no hops.
+template <typename R, int BLK>
 __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(1, 8)))
-void k_bwd_rb(const Z<RL>* __restrict__ U, Geom g, double kappa, double emu,
-                                                    Work<R> wk, SrcList L, Coef coef0, int j, int npart_in) {
+void k_bwd_rb_last(Geom g, double kappa, Work<R> wk, SrcList L, Coef coef0, int j) {
     const int e = blockIdx.y, slot = L.slot[e];
     const Coef coef = coef0.at(slot);
     const int sb = sten_block<BLK>(g);
@@ -1983,25 +1936,12 @@ void k_bwd_rb(const Z<RL>* __restrict__ U, Geom g, double kappa, double emu,
     const int a = sten_colour<BLK>();
     const int s = sb * kSites + threadIdx.x % kSites;
     const BwdCoefs cf = bwd_coefs(coef, j, j + 1 < L.k[e]);
-    // the partial sums' loads go out with the hops' loads; only the epilogue needs
-    // the sums, so they are combined after the hops
-    double red[kNvRA];
-    Z<R> accs[4], accr[4];   // field A = sbar_j at +mu, field B = rbar_j at -mu
+    const double red[kNvRA] = {};
+    Z<R> accs[4], accr[4];
     zero1(accs);
     zero1(accr);
-    if (!LAST) {
-        gather_partials<kNvRA, BLK>(wk.p(slot, 1), npart_in, red);
-        if (s < g.V) {
-            const Z<R>* fs = wk.sb(slot, j);
-            const Z<R>* fr = wk.f(slot, 4 + (j & 1));
-            const Nbr n = neighbours(g, s);
-            hop_all_pair<BLK>(accs, accr, U, fs, fr, g, s, a, n, (R)emu, (R)(1.0 / emu));
-            mem_fence_compiler();
-        }
-        block_sum<kNvRA, BLK>(red);
-    }
-    bwd_rb_finish<R, LAST, BLK>(g, kappa, wk, coef, slot, j, L.k[e], BLK == kSites ? (int)blockIdx.x : sb, a, s,
-                                red, accs, accr, cf);
+    bwd_rb_finish<R, true, BLK>(g, kappa, wk, coef, slot, j, L.k[e], BLK == kSites ? (int)blockIdx.x : sb, a, s, red,
+                                accs, accr, cf);
 }
 
 // Colour grid, not the last step: blocks of three wavefronts (kRBlock).  Wavefronts 1 and 2
@@ -2148,9 +2088,9 @@ void launch_bwd_rb(const Z<RL>* U, const Geom& g, double kappa, double mu, const
     const double emu = std::exp(mu);
     const dim3 grid(cg ? np_colour(g.V) : g.nwg, L.n);
     if (last && cg)
-        timed_launch(k_bwd_rb<R, true, kSites, RL>, grid, dim3(kSites), st, t, U, g, kappa, emu, wk, L, coef, j, np);
+        timed_launch(k_bwd_rb_last<R, kSites>, grid, dim3(kSites), st, t, g, kappa, wk, L, coef, j);
     else if (last)
-        timed_launch(k_bwd_rb<R, true, kCBlock, RL>, grid, dim3(kCBlock), st, t, U, g, kappa, emu, wk, L, coef, j, np);
+        timed_launch(k_bwd_rb_last<R, kCBlock>, grid, dim3(kCBlock), st, t, g, kappa, wk, L, coef, j);
     else if (cg)
         timed_launch(k_bwd_rb_cg<R, RL>, grid, dim3(kRBlock), st, t, U, g, kappa, emu, wk, L, coef, j, np);
     else if (ns == 4)
@@ -2559,8 +2499,8 @@ int launch_biorth(const Geom& g, const Work<R>& wk, const SrcList& L, Coef coef,
 
 // The stencil launchers for fields of type R and links of type RL.
 #define TSLOV_INST_STENCIL(R, RL)                                                                               \
-    template void launch_apply<R, RL>(const Z<RL>*, const ZD*, ZD*, const Geom&, double, double, int, \
-                                                int, hipStream_t, Timing, int);                                 \
+    template void launch_apply<R, RL>(const Z<RL>*, const ZD*, ZD*, const Geom&, double, double, int, int,      \
+                                      hipStream_t, Timing, int);                                                \
     template void launch_fwd_pair<R, RL>(const Z<RL>*, const Geom&, double, double, const Work<R>&,             \
                                          const SrcList&, Coef, int, int, int, hipStream_t, Timing);             \
     template void launch_fwd_replay<R, RL>(const Z<RL>*, const Geom&, double, double, const Work<R>&,           \

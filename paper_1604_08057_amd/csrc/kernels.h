@@ -28,8 +28,8 @@ void launch_spinor_from_soa(const Z<R>* in, ZD* out, const Geom& g, hipStream_t 
 // caller's arrays), fields rounded to R.  tm_T: the t-slices per chunk of a marching
 // lattice (0: the built-in choice; every choice gives the same result).
 template <typename R, typename RL>
-void launch_apply(const Z<RL>* U, const ZD* in, ZD* out, const Geom& g, double kappa, double mu, int g5_in,
-                            int g5_out, hipStream_t st, Timing t = {}, int tm_T = 0);
+void launch_apply(const Z<RL>* U, const ZD* in, ZD* out, const Geom& g, double kappa, double mu, int g5_in, int g5_out,
+                  hipStream_t st, Timing t = {}, int tm_T = 0);
 // The t-slices per chunk the marching operator can run this lattice with, at most maxn
 // of them into T; 0 when it does not apply.
 int tmarch_chunks(const Geom& g, int* T, int maxn);
@@ -98,8 +98,8 @@ template <typename R>
 void launch_recur(const Geom& g, const Work<R>& wk, const SrcList& L, Coef coef, int j, hipStream_t st);
 // Replay of step j for regeneration: the step's own kernels (one entry per
 // workgroup) with the recorded coefficients (beta_j, gamma_j; alpha_j) in place of
-// their reductions, rewriting v_j, w_j, a_j, b_j (fwd) and the residuals of step j
-// for entries with j < k[e] (recur) bit for bit, and no partial sums, flags or
+// their reductions, rewriting a_j, b_j (fwd; at j = 1 also the source as both residuals)
+// and the residuals r_{j+1}, s_{j+1} for entries with j < k[e] (recur) bit for bit, and no partial sums, flags or
 // coefficient records.
 template <typename R, typename RL>
 void launch_fwd_replay(const Z<RL>* U, const Geom& g, double kappa, double mu, const Work<R>& wk, const SrcList& L,
@@ -330,21 +330,18 @@ void nest_block(const NestWork& nw, const DenseWork& w2, int m, hipStream_t st);
 void nest_finish(const NestWork& nw, const DenseWork& w2, Coef coef, int k, int m, hipStream_t st);
 
 // ---------------------------------------------------------------- rational step
-// Workspace of the partial-fraction sign step (ratsign.hip): per entry of the list a
-// plane of kcap rows of ld poles, two partials per row, and acc: |dc|^2 and |c|^2, dc the
-// difference of the two members whose mean is c.
+// Workspace of the partial-fraction sign step (ratsign.hip): a plane of k rows of ld poles,
+// two partials per row, and acc: |dc|^2 and |c|^2, dc the difference of the two members
+// whose mean is c.
 struct RatWork {
-    ZD* mem;
+    ZD* buf;
     double* rows;
     double* acc;
     size_t ld;
-    int kcap;
-    __host__ __device__ ZD* buf(int e) const { return mem + (size_t)e * kcap * ld; }
-    __host__ __device__ double* part(int e) const { return rows + (size_t)e * 2 * kcap; }
 };
-// coef.c = sgn(T) e_1 of every entry (k[e] = k_used, decreasing) by the N-point rational
-// sign (N a multiple of 4), the accuracy estimates into w.acc.
-void launch_ratsign(Coef coef, const SrcList& L, const RatWork& w, int N, hipStream_t st);
+// coef.c = sgn(T) e_1 of one entry (its coefficients, k steps) by the N-point rational sign
+// (N a multiple of 4), the accuracy estimate into w.acc.
+void launch_ratsign(Coef coef, int k, const RatWork& w, int N, hipStream_t st);
 
 // out[0] = min |Re theta| over the eigenvalues theta of T_k (slot 0's coefficients, k <= 1024),
 // out[1] = its infinity norm, out[2] = sweeps of the last stage (-1: some root unsettled; -2:

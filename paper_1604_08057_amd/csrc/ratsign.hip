@@ -69,12 +69,10 @@ __device__ __forceinline__ double rat_scale(const Coef& coef, int k) {
 // from the last row up  d_j = alpha_j - t - beta_{j+1} gamma_{j+1} / d_{j+1},  then down
 // x_1 = 1 / d_1, x_j = -beta_j x_{j-1} / d_j.  A small d_j does no harm: every d_j is that of
 // a row whose alpha_j - t and beta gamma are changed by a few ulps, and the x_j are products
-// (pivots of 1e-15 planted at a pole leave c good to 1e-15).  Row j of the entry's plane (ld
-// poles): 1/d_j after the first sweep, W x_j after the second.
-__global__ __launch_bounds__(kRT) void k_rat_sweeps(Coef coef0, SrcList L, RatWork w, int N) {
+// (pivots of 1e-15 planted at a pole leave c good to 1e-15).  Row j of the plane (ld poles):
+// 1/d_j after the first sweep, W x_j after the second.
+__global__ __launch_bounds__(kRT) void k_rat_sweeps(Coef coef, int k, RatWork w, int N) {
     extern __shared__ ZD rs[];   // alpha_j, beta_j gamma_j and beta_j (index j - 1)
-    const int e = blockIdx.y, k = L.k[e];
-    const Coef coef = coef0.at(L.slot[e]);
     ZD* const al = rs;
     ZD* const bg = rs + k;
     double* const be = reinterpret_cast<double*>(rs + 2 * k);
@@ -90,7 +88,7 @@ __global__ __launch_bounds__(kRT) void k_rat_sweeps(Coef coef0, SrcList L, RatWo
     double sn, cs;
     sincospi((double)(n - (N / 2 - 1)) / N, &sn, &cs);
     const double t = s * sn / cs, W = s / (cs * cs * N);
-    ZD* const buf = w.buf(e) + n;
+    ZD* const buf = w.buf + n;
     const size_t ld = w.ld;
     ZD r = mk<double>(0, 0);
     for (int j = k - 1; j >= 0; --j) {
@@ -115,14 +113,12 @@ __global__ __launch_bounds__(kRT) void k_rat_sweeps(Coef coef0, SrcList L, RatWo
     }
 }
 
-// Pole sum of row j (block = row, entry = grid.y): c_j.  A thread's poles n, n + 256, ...
-// have one parity, so the sums signed by it give the two members' difference dc_j.
-// Row partials: |dc_j|^2, |c_j|^2.
-__global__ __launch_bounds__(kRR) void k_rat_sums(Coef coef0, SrcList L, RatWork w, int N) {
-    const int e = blockIdx.y, k = L.k[e], j = blockIdx.x;
-    if (j >= k) return;
-    const Coef coef = coef0.at(L.slot[e]);
-    const ZD* const row = w.buf(e) + (size_t)j * w.ld;
+// Pole sum of row j (block = row): c_j.  A thread's poles n, n + 256, ... have one parity,
+// so the sums signed by it give the two members' difference dc_j.  Row partials: |dc_j|^2,
+// |c_j|^2.
+__global__ __launch_bounds__(kRR) void k_rat_sums(Coef coef, int k, RatWork w, int N) {
+    const int j = blockIdx.x;
+    const ZD* const row = w.buf + (size_t)j * w.ld;
     double v[4] = {0.0, 0.0, 0.0, 0.0};
     for (int n = threadIdx.x; n < N - 1; n += kRR) {
         v[0] += row[n].re;
@@ -141,28 +137,26 @@ __global__ __launch_bounds__(kRR) void k_rat_sums(Coef coef0, SrcList L, RatWork
     if (j == 1) t = mk<double>(lin * coef.beta[2], 0.0);
     const ZD c = mk<double>(v[0], v[1]) + t, dc = mk<double>(v[2], v[3]) + t;
     coef.c[j + 1] = c;
-    double* const p = w.part(e) + 2 * j;
+    double* const p = w.rows + 2 * j;
     p[0] = norm2(dc);
     p[1] = norm2(c);
 }
 
-// |dc|^2 and |c|^2 into acc(e).
-__global__ __launch_bounds__(kRR) void k_rat_finish(SrcList L, RatWork w) {
-    const int e = blockIdx.x;
+// |dc|^2 and |c|^2 into acc.
+__global__ __launch_bounds__(kRR) void k_rat_finish(int k, RatWork w) {
     double v[2];
-    reduce_partials<2, kRR>(w.part(e), L.k[e], v);
+    reduce_partials<2, kRR>(w.rows, k, v);
     if (threadIdx.x == 0) {
-        w.acc[2 * e] = v[0];
-        w.acc[2 * e + 1] = v[1];
+        w.acc[0] = v[0];
+        w.acc[1] = v[1];
     }
 }
 
-void launch_ratsign(Coef coef, const SrcList& L, const RatWork& w, int N, hipStream_t st) {
-    const int kmax = L.k[0];
-    const size_t lds = (size_t)kmax * (2 * sizeof(ZD) + sizeof(double));
-    hipLaunchKernelGGL(k_rat_sweeps, dim3((N - 1 + kRT - 1) / kRT, L.n), dim3(kRT), lds, st, coef, L, w, N);
-    hipLaunchKernelGGL(k_rat_sums, dim3(kmax, L.n), dim3(kRR), 0, st, coef, L, w, N);
-    hipLaunchKernelGGL(k_rat_finish, dim3(L.n), dim3(kRR), 0, st, L, w);
+void launch_ratsign(Coef coef, int k, const RatWork& w, int N, hipStream_t st) {
+    const size_t lds = (size_t)k * (2 * sizeof(ZD) + sizeof(double));
+    hipLaunchKernelGGL(k_rat_sweeps, dim3((N - 1 + kRT - 1) / kRT), dim3(kRT), lds, st, coef, k, w, N);
+    hipLaunchKernelGGL(k_rat_sums, dim3(k), dim3(kRR), 0, st, coef, k, w, N);
+    hipLaunchKernelGGL(k_rat_finish, dim3(1), dim3(kRR), 0, st, k, w);
 }
 
 }  // namespace tslov

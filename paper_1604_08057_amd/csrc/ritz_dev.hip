@@ -303,7 +303,8 @@ __global__ __launch_bounds__(kGroupThreads) void k_ritz(Coef coef, int k, int nd
 
 // One sweep at depth d, 128 roots per workgroup (a wavefront per SIMD: the chain is all
 // latency); the first one starts from the roots of the halved blocks.  Every operand is
-// loaded ahead of the first test: one round trip.
+// loaded ahead of the first test, all in one round trip (the compiler holds them in private
+// memory until then, 256 bytes per thread).
 constexpr int kSweepBlock = 256, kSweepRows = 4;   // k <= 1024
 __global__ __launch_bounds__(kSweepBlock) void k_ritz_sweep(double* __restrict__ out, int k, int d, int cur,
                                                             int first) {
