@@ -143,7 +143,7 @@ struct tslov_ctx {
     hipStream_t st = nullptr;
     hipStream_t side = nullptr;   // the sign calls' Ritz values, beside the projected-matrix step
     int device = 0;
-    void* noalloc_in = nullptr;   // this device's noalloc_input
+    void* noalloc_in = nullptr;   // this device's noalloc_input, looked up when first needed (13 ms)
     size_t lds_max = 65536;
     int links_set = 0;
     int diag = 0;    // tslov_set_diagnostics flags
@@ -2099,11 +2099,8 @@ tslov_status tslov_create(const tslov_lattice_desc* d, void* stream, tslov_ctx**
     HIPCHK(hipGetDevice(&dev));
     hipDeviceProp_t prop;
     HIPCHK(hipGetDeviceProperties(&prop, dev));
-    void* noalloc_in = nullptr;
-    HIPCHK(hipGetSymbolAddress(&noalloc_in, HIP_SYMBOL(noalloc_input)));
     tslov_ctx* c = new tslov_ctx();
     c->device = dev;
-    c->noalloc_in = noalloc_in;
     c->lds_max = prop.sharedMemPerBlock ? prop.sharedMemPerBlock : 65536;
     c->g.nx = d->dims[0];
     c->g.ny = d->dims[1];
@@ -2187,6 +2184,7 @@ static tslov_status apply_op(tslov_ctx* c, const void* in, void* out, double mu,
     const uintptr_t a = (uintptr_t)in, b = (uintptr_t)out;
     if ((a < b ? b - a : a - b) < bytes) {
         if (!no_alloc) CHK(ensure(c->opin, bytes));
+        else if (!c->noalloc_in) HIPCHK(hipGetSymbolAddress(&c->noalloc_in, HIP_SYMBOL(noalloc_input)));
         void* copy = no_alloc ? c->noalloc_in : c->opin.p;
         HIPCHK(hipMemcpyAsync(copy, in, bytes, hipMemcpyDeviceToDevice, c->st));
         in = copy;

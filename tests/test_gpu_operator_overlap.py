@@ -40,3 +40,31 @@ def test_overlapping_output(dims, precision, entry):
     assert call(ctx.handle, ptr(src), ptr(src), 0) != 0   # the same array stays refused
     ctx.close()
     say(f"overlapping output {entry} {dims} {precision}")
+
+
+def test_overlapping_output_captured():
+    """The allocation-free entry as a graph, its copy of the input included, replayed on new inputs."""
+    from paper_1604_08057_amd import Context
+    dims, V = (16, 8, 8, 8), 8192
+    rng = np.random.default_rng(6)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        ctx = Context(dims, -2.0, 0.3)
+        ctx.set_links(dev(random_links(dims, 0.4, rng)))
+        xs = [dev(z2_complex_source(V, rng)) for _ in range(3)]
+        wants = [ctx.apply_h(x) for x in xs]
+        buf = torch.zeros((V + 1, 4, 3), dtype=torch.complex128, device="cuda")
+    st.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        rc = ctx.lib.tslov_apply_h_noalloc(ctx.handle, ctypes.c_void_p(buf.data_ptr()),
+                                           ctypes.c_void_p(buf[1:].data_ptr()), 0)
+    assert rc == 0
+    for x, want in zip(xs, wants):
+        buf[:V].copy_(x)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(buf[1:], want)
+    del graph
+    ctx.close()
