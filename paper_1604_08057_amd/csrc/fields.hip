@@ -1380,8 +1380,10 @@ __device__ __forceinline__ bool blk_scalars(const Coef& coef, int j, const doubl
             return false;
         }
     }
-    const double beta = sqrt(aom);
-    const ZD gam = (1.0 / beta) * om;
+    // |x| from its square itself: |omega| takes the fourth power, which leaves the range for
+    // sources beyond 1e+-77
+    const double beta = j == 1 ? sqrt(red[2]) : sqrt(aom);
+    const ZD gam = j == 1 ? mk<double>(beta, 0.0) : (1.0 / beta) * om;
     if (writer) {
         coef.beta[j] = beta;
         coef.gamma[j] = gam;
@@ -1389,7 +1391,7 @@ __device__ __forceinline__ bool blk_scalars(const Coef& coef, int j, const doubl
         if (j == 1) coef.misc[0] = beta;
     }
     ib = 1.0 / beta;
-    icg = zdiv(mk<double>(1.0, 0.0), cj(gam));
+    icg = j == 1 ? mk<double>(ib, 0.0) : zdiv(mk<double>(1.0, 0.0), cj(gam));
     return true;
 }
 
